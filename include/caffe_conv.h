@@ -131,6 +131,20 @@ int caffe_conv_workspace_size(const caffe_conv_desc* desc, int32_t pass, size_t*
  * pass (caffe_last_error() then says why).  Host-only. */
 size_t caffe_conv_workspace_bytes(const caffe_conv_desc* desc, int32_t pass);
 
+/* Bytes of workspace with which `pass` runs its fastest kernels (at least
+ * caffe_conv_workspace_size).  Large CAFFE_F32 convolutions run on the bf16
+ * matrix instructions, each float operand staged in the workspace as the exact
+ * sum of three bf16 terms (products, sums and results keep float precision);
+ * with a workspace of at least caffe_conv_workspace_size but less than this
+ * they run on the float instructions, which stage nothing.  The two forms
+ * differ by rounding.  Host-only. */
+int caffe_conv_workspace_preferred(const caffe_conv_desc* desc, int32_t pass, size_t* bytes);
+
+/* 1 when `pass` (forward, data, weights, or backward: both gradients) runs on
+ * three-term operands given caffe_conv_workspace_preferred bytes, else 0 (also
+ * for an invalid descriptor).  Host-only. */
+int caffe_conv_uses_terms(const caffe_conv_desc* desc, int32_t pass);
+
 /* Forward pass (Sec. 3.2): top = [relu](weight (*) bottom + bias).
  * bias may be NULL (no bias).  top is overwritten. */
 int caffe_conv_forward(const caffe_conv_desc* desc, const void* bottom, const void* weight,
@@ -216,7 +230,13 @@ enum caffe_backward_flags {
     /* caffe_conv_backward_pool_lrn(_ex) (caffe_layers.h) only: pool_mask
      * holds one byte per pooled value, as caffe_pool_lrn_forward writes it
      * with CAFFE_POOL_MASK_OFFSETS. */
-    CAFFE_BACKWARD_POOL_MASK_OFFSETS = 32
+    CAFFE_BACKWARD_POOL_MASK_OFFSETS = 32,
+    /* CAFFE_F32 mode: as CAFFE_BACKWARD_BOTTOM_STAGED for the three-term
+     * staging of bottom (caffe_conv_workspace_preferred) that the last
+     * caffe_conv_forward with the same descriptor, bottom, workspace and
+     * ws_bytes left in the workspace, nothing of which has changed since.
+     * No effect where either pass runs on the float instructions. */
+    CAFFE_BACKWARD_BOTTOM_TERMS = 64
 };
 
 /* The whole backward pass of the layer in one call: the ReLU mask is applied

@@ -16,6 +16,7 @@ import torch
 from . import _lib
 from ._lib import (  # noqa: F401
     CAFFE_ERR_UNSUPPORTED, CAFFE_ERR_WORKSPACE, NOALLOC_SCRATCH_BYTES, BACKWARD_BOTTOM_STAGED,
+    BACKWARD_BOTTOM_TERMS,
     BACKWARD_MASK_BOTTOM_DIFF, BACKWARD_POOL_MASK_OFFSETS, BACKWARD_TOP_DIFF_MASKED,
     BACKWARD_TOP_STAGED,
     FORWARD_BOTTOM_STAGED, CAFFE_BF16, CAFFE_BF16_F32_BOTTOM, CAFFE_F32, CAFFE_LR_EXP,
@@ -26,7 +27,7 @@ from ._lib import (  # noqa: F401
 )
 
 __all__ = [
-    "conv_desc", "conv_out_shape", "conv_workspace_size", "conv_forward", "conv_backward",
+    "conv_desc", "conv_out_shape", "conv_workspace_size", "conv_workspace_preferred", "conv_uses_terms", "conv_forward", "conv_backward",
     "conv_backward_data", "conv_backward_weights", "maxpool_forward", "maxpool_backward",
     "lrn_forward", "lrn_backward", "cast_f32_to_bf16", "Workspace", "CaffeError",
     "sgd_learning_rate", "softmax_loss", "sgd_update", "pool_lrn_forward", "lrn_pool_backward",
@@ -60,6 +61,18 @@ def conv_workspace_size(desc, pass_):
     n = ctypes.c_size_t()
     check(load().caffe_conv_workspace_size(ctypes.byref(desc), int(pass_), ctypes.byref(n)))
     return n.value
+
+
+def conv_workspace_preferred(desc, pass_):
+    """Bytes of workspace with which the pass runs its fastest kernels."""
+    n = ctypes.c_size_t()
+    check(load().caffe_conv_workspace_preferred(ctypes.byref(desc), int(pass_), ctypes.byref(n)))
+    return n.value
+
+
+def conv_uses_terms(desc, pass_):
+    """Whether the pass runs on three-term operands given its preferred workspace."""
+    return bool(load().caffe_conv_uses_terms(ctypes.byref(desc), int(pass_)))
 
 
 def _ptr(t):
@@ -199,10 +212,9 @@ def _dtype_of(x, w):
 def conv_forward(x, w, b=None, stride=1, pad=0, group=1, relu=False, out=None, ws=None):
     dtype = _dtype_of(x, w)
     d = conv_desc(x.shape, w.shape, stride, pad, group, relu, dtype)
-    Ho, Wo = conv_out_shape(d)
     if out is None:
-        out = torch.empty((d.N, d.K, Ho, Wo), dtype=torch.float32, device=x.device)
-    need = conv_workspace_size(d, PASS_FORWARD)
+        out = torch.empty((d.N, d.K) + conv_out_shape(d), dtype=torch.float32, device=x.device)
+    need = conv_workspace_preferred(d, PASS_FORWARD)
     buf = (ws or Workspace(x.device)).get(need)
     caffe_conv_forward(d, x, w, b, out, buf)
     return out
@@ -220,7 +232,7 @@ def conv_backward(x, w, top_diff, top=None, stride=1, pad=0, group=1, relu=False
         db = torch.empty((w.shape[0],), dtype=torch.float32, device=dev) if "db" in need else None
     else:
         dx, dw, db = outs
-    buf = (ws or Workspace(dev)).get(conv_workspace_size(d, PASS_BACKWARD))
+    buf = (ws or Workspace(dev)).get(conv_workspace_preferred(d, PASS_BACKWARD))
     need_x = dw is not None or (flags & BACKWARD_MASK_BOTTOM_DIFF)
     caffe_conv_backward(d, top_diff, top, x if need_x else None, w if dx is not None else None,
                         dx, dw, db, accumulate, flags, buf)
@@ -232,7 +244,7 @@ def conv_backward_data(x_shape, w, top_diff, top=None, stride=1, pad=0, group=1,
     dtype = CAFFE_BF16 if w.dtype == torch.bfloat16 else CAFFE_F32
     d = conv_desc(x_shape, w.shape, stride, pad, group, relu, dtype)
     dx = torch.empty(tuple(x_shape), dtype=torch.float32, device=top_diff.device)
-    buf = (ws or Workspace(top_diff.device)).get(conv_workspace_size(d, PASS_BACKWARD_DATA))
+    buf = (ws or Workspace(top_diff.device)).get(conv_workspace_preferred(d, PASS_BACKWARD_DATA))
     caffe_conv_backward_data(d, top_diff, top, w, dx, buf)
     return dx
 
@@ -243,7 +255,7 @@ def conv_backward_weights(x, w_shape, top_diff, top=None, stride=1, pad=0, group
     d = conv_desc(x.shape, w_shape, stride, pad, group, relu, dtype)
     dw = torch.empty(tuple(w_shape), dtype=torch.float32, device=x.device)
     db = torch.empty((w_shape[0],), dtype=torch.float32, device=x.device) if with_bias else None
-    buf = (ws or Workspace(x.device)).get(conv_workspace_size(d, PASS_BACKWARD_WEIGHTS))
+    buf = (ws or Workspace(x.device)).get(conv_workspace_preferred(d, PASS_BACKWARD_WEIGHTS))
     caffe_conv_backward_weights(d, top_diff, top, x, dw, db, accumulate, buf)
     return dw, db
 

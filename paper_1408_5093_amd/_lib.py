@@ -26,6 +26,7 @@ BACKWARD_MASK_BOTTOM_DIFF = 2
 BACKWARD_BOTTOM_STAGED = 4
 BACKWARD_TOP_STAGED = 16
 BACKWARD_POOL_MASK_OFFSETS = 32
+BACKWARD_BOTTOM_TERMS = 64
 FORWARD_BOTTOM_STAGED = 1
 POOL_RELU_INPUT = 1
 POOL_LRN_STAGE_ONLY = 2
@@ -53,7 +54,8 @@ EXPORTS = (
     "caffe_lrn_forward", "caffe_lrn_backward", "caffe_cast_f32_to_bf16",
     "caffe_sgd_learning_rate", "caffe_softmax_loss", "caffe_sgd_update",
     "caffe_pool_lrn_forward", "caffe_lrn_pool_backward", "caffe_sgd_update_device_lr",
-    "caffe_conv_workspace_bytes", "caffe_conv_status_string", "caffe_conv_forward_noalloc",
+    "caffe_conv_workspace_bytes", "caffe_conv_workspace_preferred",
+    "caffe_conv_uses_terms", "caffe_conv_status_string", "caffe_conv_forward_noalloc",
     "caffe_conv_backward_pool_lrn", "caffe_relu_backward", "caffe_conv_backward_ex",
     "caffe_conv_backward_pool_lrn_ex", "caffe_conv_backward_into",
     "caffe_conv_stage_below_supported", "caffe_conv_forward_ex", "caffe_pool_lrn_forward_into",
@@ -112,6 +114,8 @@ def load():
     sig = {
         "caffe_conv_out_shape": [cdp, pi32, pi32],
         "caffe_conv_workspace_size": [cdp, i32, ctypes.POINTER(sz)],
+        "caffe_conv_workspace_preferred": [cdp, i32, ctypes.POINTER(sz)],
+        "caffe_conv_uses_terms": [cdp, i32],
         "caffe_conv_forward": [cdp, vp, vp, vp, vp, vp, sz, vp],
         "caffe_conv_forward_ex": [cdp, vp, vp, vp, vp, vp, sz, i32, vp],
         "caffe_conv_forward_noalloc": [cdp, vp, vp, vp, vp, vp],

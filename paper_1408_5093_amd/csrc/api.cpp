@@ -117,6 +117,22 @@ struct ConvPlan {
         int T, splits, sps, c0;
         int64_t bytes;
     } fwd_tail, dgrad_tail;
+    // float operands as three bf16 terms (conv_triple.hip), pass by pass where
+    // it is the faster path and the workspace holds its staging
+    struct X3 {
+        bool fwd, data, wgt, wgt_joint;  // joint: with the data gradient in one call
+        int Cgp, Kgp, XHp, XWp, DHp, DWp, dtb, dlb, doh0, dow0;
+        int RuF, RuD, Rw;  // units per packed weight row; weight-gradient columns
+        int fwd_tile, data_tile, wgt_tile;
+        int fwd_splits, fwd_sps, data_splits, data_sps;
+        Tail fwd_tail, data_tail;
+        int splits, cols_per_split;
+        // forward: [X][Wp][partials]; backward: [X][D][sums][Wt][data
+        // partials][weight partials], then the float path's regions where a
+        // pass stays there; X (weight gradient) where the forward leaves it
+        size_t off_wp, off_fpart, ws_fwd;
+        size_t off_d, off_sums, off_wt, off_dpart, off_wpart, off_float, ws_back;
+    } x3;
     bool dense;
     int fc_tile_f, fc_tile_d, fc_tile_w;
     int fc_splits_f, fc_sps_f, fc_splits_d, fc_sps_d, fc_splits_w, fc_sps_w;
@@ -129,6 +145,11 @@ struct ConvPlan {
 bool is_bf16(const ConvPlan& q) { return q.dtype != CAFFE_F32; }
 bool bottom_f32(const ConvPlan& q) { return q.dtype != CAFFE_BF16; }
 
+double plan_splits_tile(int M, int ncol, int64_t nst, int tm, int tn, double t_stage, int cus,
+                        int forced, int* splits, int* sps, int groups);
+double plan_tail_tile(int M, int64_t ncol, int64_t nst, int tm, int tn, double t_stage, int G,
+                      int cus, int forced, int forced_cus, ConvPlan::Tail* t);
+
 // Split-K plan of a dense GEMM with M rows, ncol columns and a reduction of R
 // on `cus` compute units.  Workgroups are dealt evenly to the units and a
 // unit works through its share at its MFMA rate, so the GEMM takes about
@@ -139,18 +160,26 @@ bool bottom_f32(const ConvPlan& q) { return q.dtype != CAFFE_BF16; }
 // add s * groups * M * ncol partial sums written and read back once.  The
 // plan takes the s with the least modelled time (ties: fewer splits), and
 // splits only when that time is at least 10% below the unsplit one.
-void plan_splits(int M, int ncol, int R, int tile, int cus, int forced, int* splits, int* sps,
-                 int groups = 1)
+double plan_splits(int M, int ncol, int R, int tile, int cus, int forced, int* splits, int* sps,
+                   int groups = 1)
 {
     const int tm = gemm_tile_m(tile), tn = gemm_tile_n(tile), tk = gemm_tile_k(tile);
+    // one workgroup-stage at ~85% of a unit's fp32 MFMA rate (157.3 TFLOP/s
+    // over 256 units)
+    const double t_stage = 2.0 * tm * tn * tk / (0.85 * 157.3e12 / 256);
+    return plan_splits_tile(M, ncol, std::max(1, (R + tk - 1) / tk), tm, tn, t_stage, cus, forced,
+                            splits, sps, groups);
+}
+
+// plan_splits for tiles of tm x tn whose workgroups take t_stage per stage,
+// nst stages in all; returns the modelled time of the plan.
+double plan_splits_tile(int M, int ncol, int64_t nst, int tm, int tn, double t_stage, int cus,
+                        int forced, int* splits, int* sps, int groups)
+{
     const int64_t tiles = std::max<int64_t>(
         1, (int64_t)groups * ((M + tm - 1) / tm) * ((ncol + tn - 1) / tn));
-    const int64_t nst = std::max(1, (R + tk - 1) / tk);
     cus = std::max(1, cus);
-    // one workgroup-stage at ~85% of a unit's fp32 MFMA rate (157.3 TFLOP/s
-    // over 256 units), partials at ~4 TB/s
-    const double t_stage = 2.0 * tm * tn * tk / (0.85 * 157.3e12 / 256);
-    const double t_byte = 1.0 / 4e12;
+    const double t_byte = 1.0 / 4e12;  // partials at ~4 TB/s
     int64_t best = 1;
     double best_t = -1, t1 = 0;
     for (int64_t sp = 1; sp <= nst; ++sp) {
@@ -175,6 +204,7 @@ void plan_splits(int M, int ncol, int R, int tile, int cus, int forced, int* spl
         best = std::min<int64_t>(forced, nst);
     *sps = (int)((nst + best - 1) / best);
     *splits = (int)((nst + *sps - 1) / *sps);
+    return best > 1 ? best_t : t1;
 }
 
 // Tail split of a GEMM with G groups of M x ncol outputs on a tile and a
@@ -194,35 +224,47 @@ void plan_splits(int M, int ncol, int R, int tile, int cus, int forced, int* spl
 // gradient 0.719 -> 0.661, conv2's forward 0.929 -> 0.908 with 2, conv2's
 // data gradient 1.032 -> 0.993 with 4; conv1's data gradient, which the
 // model leaves whole, 0.630 -> 0.652 with 2).
-void plan_tail(int M, int64_t ncol, int R, int tile, int G, int cus, int forced, int forced_cus,
-               ConvPlan::Tail* t)
+double plan_tail(int M, int64_t ncol, int R, int tile, int G, int cus, int forced, int forced_cus,
+                 ConvPlan::Tail* t)
+{
+    const int tm = gemm_tile_m(tile), tn = gemm_tile_n(tile), tk = gemm_tile_k(tile);
+    return plan_tail_tile(M, ncol, (R + tk - 1) / tk, tm, tn,
+                          2.0 * tm * tn * tk / (0.8 * 157.3e12 / 256), G, cus, forced, forced_cus,
+                          t);
+}
+
+// (as plan_tail; returns the modelled time of the plan, 0 without a tail)
+double plan_tail_tile(int M, int64_t ncol, int64_t nst, int tm, int tn, double t_stage, int G,
+                      int cus, int forced, int forced_cus, ConvPlan::Tail* t)
 {
     *t = ConvPlan::Tail{0, 1, 0, 0, 0};
-    const int tm = gemm_tile_m(tile), tn = gemm_tile_n(tile), tk = gemm_tile_k(tile);
     const int64_t n_mt = (M + tm - 1) / tm, n_ct = (ncol + tn - 1) / tn;
     const int64_t n_tiles = n_mt * n_ct * G;
-    const int64_t nst = (R + tk - 1) / tk;
     if (forced_cus > 0)  // profiling and tests only
         cus = forced_cus;
     cus = std::max(1, cus);
     if (forced == 0 || n_tiles < cus || nst < 8 || M <= 0)
-        return;
+        return 0;
     const int64_t past = n_tiles % cus;
     if (past == 0 && forced < 0)
-        return;
+        return 0;
     // whole column tiles of the last group
     const int64_t n_tail = std::max<int64_t>(n_mt, (past + n_mt - 1) / n_mt * n_mt);
     if (n_tail > n_mt * n_ct)
-        return;
+        return 0;
     const int64_t full = n_tiles - n_tail;
-    const double t_stage = 2.0 * tm * tn * tk / (0.8 * 157.3e12 / 256);
-    auto unit_time = [&](int64_t s) {  // the busiest unit's stages
+    // the busiest unit's stages: whole tiles on units 0 .. full % cus - 1 are
+    // one more, and so are the partial ones on the run of units from full %
+    // cus on, so the maximum is at the ends of those runs
+    auto unit_time = [&](int64_t s) {
         const int64_t sps = (nst + s - 1) / s;
+        const int64_t lo = full, hi = full + n_tail * s;
+        const int64_t ends[] = {0, lo % cus, (lo + cus - 1) % cus, hi % cus, (hi + cus - 1) % cus,
+                                cus - 1};
         int64_t worst = 0;
-        for (int64_t c = 0; c < cus; ++c) {
+        for (const int64_t c : ends) {
             const int64_t nf = full > c ? (full - 1 - c) / cus + 1 : 0;
             // partial workgroups b = full .. full + n_tail * s - 1 on unit c
-            const int64_t lo = full, hi = full + n_tail * s;
             const int64_t first = lo + ((c - lo % cus) % cus + cus) % cus;
             const int64_t np = first < hi ? (hi - 1 - first) / cus + 1 : 0;
             worst = std::max(worst, nf * nst + np * sps);
@@ -244,12 +286,13 @@ void plan_tail(int M, int64_t ncol, int R, int tile, int G, int cus, int forced,
         }
     }
     if (best < 2)
-        return;
+        return 0;
     t->T = (int)full;
     t->splits = (int)best;
     t->sps = (int)((nst + best - 1) / best);
     t->c0 = (int)((n_ct - n_tail / n_mt) * tn);
     t->bytes = best * (int64_t)M * (ncol - t->c0) * 4;
+    return best_t;
 }
 
 // Tile for a GEMM with M rows: the least padding of M; ties go to the first
@@ -311,11 +354,17 @@ int pick_wgrad_tile(int Kg, int forced)
 // are read only while CAFFE_PROFILE_OVERRIDES=1 is set, so that a stray
 // CAFFE_* variable cannot change what a default call runs (the kernel, the
 // split count and with it the summation order).
-bool overrides_enabled()
+// The switch is read once per plan: a plan looks up some twenty variables,
+// and each getenv walks the environment.
+thread_local bool g_overrides = false;
+
+void refresh_overrides()
 {
     const char* v = getenv("CAFFE_PROFILE_OVERRIDES");
-    return v && v[0] == '1' && v[1] == '\0';
+    g_overrides = v && v[0] == '1' && v[1] == '\0';
 }
+
+bool overrides_enabled() { return g_overrides; }
 
 int env_tile(const char* name)
 {
@@ -361,6 +410,41 @@ int pick_bf16_tile(int M, int forced)
     for (int t : order) {
         const int tm = bf16_tile_m(t);
         const int64_t rows = (int64_t)(M + tm - 1) / tm * tm;
+        if (rows < best_rows) {
+            best = t;
+            best_rows = rows;
+        }
+    }
+    return best;
+}
+
+// Three-term GEMM tiles: the least row padding, ties to the taller tile.
+int pick_x3_tile(int M, int forced)
+{
+    if (forced >= 0 && forced < X3TILE_COUNT)
+        return forced;
+    int best = X3TILE_128x256;
+    int64_t best_rows = INT64_MAX;
+    for (int t = 0; t < X3TILE_COUNT; ++t) {
+        const int tm = x3_tile_m(t);
+        const int64_t rows = (int64_t)(M + tm - 1) / tm * tm;
+        if (rows < best_rows) {
+            best = t;
+            best_rows = rows;
+        }
+    }
+    return best;
+}
+
+int pick_x3_wgrad_tile(int Kg, int forced)
+{
+    if (forced >= 0 && forced < X3WTILE_COUNT)
+        return forced;
+    int best = X3WTILE_128x256;
+    int64_t best_rows = INT64_MAX;
+    for (int t = 0; t < X3WTILE_COUNT; ++t) {
+        const int tm = x3_wgrad_tile_m(t);
+        const int64_t rows = (int64_t)(Kg + tm - 1) / tm * tm;
         if (rows < best_rows) {
             best = t;
             best_rows = rows;
@@ -518,8 +602,189 @@ int plan_bf16(ConvPlan* p)
     return CAFFE_OK;
 }
 
+// The three-term plan of a float convolution (conv_triple.hip): staging
+// sizes, tiles and splits, and for each pass whether it takes that path.
+// Never for shapes past the staging's limits (rows of at most 256 pixels,
+// buffers below 2^31 bytes), nor while a float kernel's tuning override is
+// set, so that those keep selecting what they name.  est_*: the float
+// kernels' modelled times.
+void plan_x3(ConvPlan* p, double est_f, double est_d, double est_w)
+{
+    ConvPlan& q = *p;
+    ConvPlan::X3& x = q.x3;
+    x = ConvPlan::X3{};
+    const int forced = env_tile("CAFFE_CONV_X3");  // bits: 1 forward, 2 data, 4 weights
+    if (forced < 0 && overrides_enabled()) {
+        static const char* const names[] = {
+            "CAFFE_CONV_FWD_TILE", "CAFFE_CONV_DGRAD_TILE", "CAFFE_CONV_WGRAD_TILE",
+            "CAFFE_CONV_WGRAD_BLOCKS", "CAFFE_CONV_WGRAD_UNIT_ORDER", "CAFFE_CONV_BLOCKED",
+            "CAFFE_CONV_XCD_ORDER", "CAFFE_CONV_WGRAD_XCD_ORDER", "CAFFE_CONV_WGRAD_QUAD",
+            "CAFFE_CONV_WGRAD_DMA", "CAFFE_CONV_FWD_SPLITS", "CAFFE_CONV_DGRAD_SPLITS",
+            "CAFFE_CONV_TAIL_SPLITS", "CAFFE_CONV_TAIL_UNITS", "CAFFE_CONV_TAP_TABLE"};
+        for (const char* n : names)
+            if (env_tile(n) >= 0)
+                return;
+    }
+    if (forced == 0 || q.N == 0 || q.W > 256 || q.Wo > 256)
+        return;
+    x.Cgp = round_up(q.Cg, 8);
+    x.Kgp = round_up(q.Kg, 8);
+    x.XHp = std::max(q.ph + q.H, (q.Ho - 1) * q.sh + q.kh);
+    x.XWp = std::max(q.pw + q.W, (q.Wo - 1) * q.sw + q.kw);
+    const int php = q.Th - 1 - q.a0h, pwp = q.Tw - 1 - q.a0w;
+    x.dtb = std::max(php, 0);
+    x.dlb = std::max(pwp, 0);
+    x.doh0 = x.dtb - php;
+    x.dow0 = x.dlb - pwp;
+    x.DHp = std::max(x.dtb + q.Ho, q.Ah + q.Th - 1 + x.doh0);
+    x.DWp = std::max(x.dlb + q.Wo, q.Aw + q.Tw - 1 + x.dow0);
+    const int Ctot = q.G * x.Cgp, Ktot = q.G * x.Kgp;
+    const int64_t xb = (int64_t)q.N * x.XHp * x.XWp * Ctot * 6;
+    const int64_t db = (int64_t)q.N * x.DHp * x.DWp * Ktot * 6;
+    const int64_t ruf = ((int64_t)q.kh * q.kw * x.Cgp / 8 + 3) / 4 * 4;
+    const int64_t rud = ((int64_t)q.Th * q.Tw * x.Kgp / 8 + 3) / 4 * 4;
+    const int64_t wpb = q.K * ruf * 48, wtb = (int64_t)q.G * q.Mt * rud * 48;
+    const int64_t rw = (int64_t)q.kh * q.kw * x.Cgp;
+    const bool fits_x = xb <= kMaxTensorBytes, fits_d = db <= kMaxTensorBytes;
+    const int64_t ncol = (int64_t)q.N * q.Ho * q.Wo, dcols = (int64_t)q.N * q.Ah * q.Aw;
+    const int cus = device_cu_count();
+    x.RuF = (int)ruf;
+    x.RuD = (int)rud;
+    x.Rw = (int)rw;
+    // (shapes too small for any pass to gain, by the rule below without its
+    // GEMM term, are not planned further)
+    const double us = 1e-6, bx = (double)q.bottom_elems * 4, bt = (double)q.top_elems * 4;
+    const double of_f = 22 * us + (bx + xb) * 2.75e-13, of_d = 21 * us + (bt + db) * 2.7e-13;
+    const double of_w = 21 * us + (2 * bt + db) * 2.1e-13 + (bx + xb) * 3e-13;
+    const double float_f = 0.88 * (14 * us + 1.25 * est_f), float_d = 0.95 * (19 * us + 1.37 * est_d);
+    const double float_w = 0.95 * (18 * us + 0.87 * est_w + bt * 5.9e-13);
+    if (forced < 0 && of_f >= float_f && of_d >= float_d && of_w >= float_w)
+        return;
+    // one workgroup-stage (32 channels, six products) at the rate a unit
+    // reaches
+    const double rate = 1.2e15 / 256;
+    auto t_stage = [&](int tm, int tn) { return 2.0 * tm * tn * kX3TK * 6 / rate; };
+
+    bool can_f = fits_x && wpb <= kMaxTensorBytes;
+    bool can_d = fits_d && wtb <= kMaxTensorBytes;
+    bool can_w = fits_x && fits_d && rw * q.K * 4 <= kMaxTensorBytes;
+    x.fwd_tile = pick_x3_tile(q.Kg, env_tile("CAFFE_X3_FWD_TILE"));
+    x.data_tile = pick_x3_tile(q.Mt, env_tile("CAFFE_X3_DGRAD_TILE"));
+    double tx_f = 0, tx_d = 0, tx_w = 0;  // modelled GEMM times
+    auto plan_gemm = [&](int M, int64_t ncols, int64_t nst, int tile, const char* env, int* splits,
+                         int* sps, ConvPlan::Tail* tail, double* time) {
+        // whichever of an even split and a tail split the models put first
+        const int tm = x3_tile_m(tile), tn = x3_tile_n(tile);
+        const int fs = env_tile(env), ft = env_tile("CAFFE_X3_TAIL_SPLITS");
+        const double ts = plan_splits_tile(M, (int)ncols, nst, tm, tn, t_stage(tm, tn), cus,
+                                           fs, splits, sps, q.G);
+        *tail = ConvPlan::Tail{0, 1, 0, 0, 0};
+        const double tt =
+            fs > 0 ? 0.0
+                   : plan_tail_tile(M, ncols, nst, tm, tn, t_stage(tm, tn), q.G, cus, ft,
+                                    env_tile("CAFFE_X3_TAIL_UNITS"), tail);
+        *time = ts;
+        if (tail->splits > 1 && (*splits == 1 || tt < ts || ft > 1)) {
+            *splits = 1;
+            *sps = (int)nst;
+            *time = tt;
+        } else {
+            *tail = ConvPlan::Tail{0, 1, 0, 0, 0};
+        }
+        const int64_t part = *splits > 1 ? (int64_t)*splits * q.G * M * ncols * 4 : tail->bytes;
+        return part <= kMaxTensorBytes ? part : -1;
+    };
+    const int64_t fpart = plan_gemm(q.Kg, ncol, x.RuF / 4, x.fwd_tile, "CAFFE_X3_FWD_SPLITS",
+                                    &x.fwd_splits, &x.fwd_sps, &x.fwd_tail, &tx_f);
+    const int64_t dpart = plan_gemm(q.Mt, dcols, x.RuD / 4, x.data_tile, "CAFFE_X3_DGRAD_SPLITS",
+                                    &x.data_splits, &x.data_sps, &x.data_tail, &tx_d);
+    can_f = can_f && fpart >= 0;
+    can_d = can_d && dpart >= 0;
+
+    // weight gradient: split-K over the output pixels; the split count with
+    // the least modelled time, whole rounds of the units times the stages of
+    // a split, plus the partials' traffic (written and read once at ~4 TB/s)
+    x.wgt_tile = pick_x3_wgrad_tile(q.Kg, env_tile("CAFFE_X3_WGRAD_TILE"));
+    const int wtm = x3_wgrad_tile_m(x.wgt_tile);
+    const int64_t tiles = (int64_t)((q.Kg + wtm - 1) / wtm) * ((rw + 255) / 256) * q.G;
+    const int64_t max_splits = std::max<int64_t>(
+        1, std::min(ncol / (4 * kX3TK), kMaxTensorBytes / std::max<int64_t>(1, rw * q.K * 4)));
+    int64_t splits = 1;
+    {
+        double best = 1e30;
+        const int64_t hi = std::min<int64_t>(max_splits, (4 * (int64_t)cus + tiles - 1) / tiles);
+        // at least a quarter of the float path's splits: a partial sum's error
+        // grows with the root of its length, and at four times the float
+        // kernel's length it is still the smaller one (measured against 64
+        // bits: conv2's weight gradient 4.3e-7 against 5.1e-7)
+        const int64_t lo = std::max<int64_t>(1, std::min<int64_t>(max_splits, (q.splits + 3) / 4));
+        for (int64_t sp = lo; sp <= std::max(lo, hi); ++sp) {
+            const int64_t rounds = (tiles * sp + cus - 1) / cus;
+            const int64_t nst = ((ncol + sp - 1) / sp + kX3TK - 1) / kX3TK;
+            const double t = rounds * (nst + 6) * t_stage(wtm, 256) + 8.0 * sp * rw * q.K / 4e12;
+            if (t < best) {
+                best = t;
+                splits = sp;
+            }
+        }
+        tx_w = best;
+        if (env_tile("CAFFE_X3_WGRAD_SPLITS") > 0)
+            splits = std::min<int64_t>(max_splits, env_tile("CAFFE_X3_WGRAD_SPLITS"));
+    }
+    int64_t cps = (ncol + splits - 1) / splits;
+    cps = std::max<int64_t>(kX3TK, (cps + kX3TK - 1) / kX3TK * kX3TK);
+    splits = std::max<int64_t>(1, (ncol + cps - 1) / cps);
+    const int64_t wpart = splits * rw * q.K * 4;
+    can_w = can_w && wpart <= kMaxTensorBytes;
+    x.splits = (int)splits;
+    x.cols_per_split = (int)cps;
+
+    // Which path is faster: both paths' times were fitted (launches, the
+    // plans' modelled GEMM time, staged bytes) to calls measured on 61
+    // shapes, CaffeNet's at N = 4 .. 64 and drawn ones of 0.3 to 60 GFLOP: the
+    // fits are within 6-17% in the mean, and no shape they choose the terms
+    // for measured slower on them (e.g. forward of 13 x 13, 192 -> 192
+    // channels: N = 4 31 us float / 35 terms, N = 16 66 / 43, N = 64 176 / 98;
+    // 1 x 1 kernels, little work per staged byte, 36 / 59).  The weight
+    // gradient of a call that also forms the data gradient shares its staged
+    // top gradient (wgt_joint).
+    const bool f = of_f + 0.62 * tx_f < float_f;
+    const bool d = of_d + 0.76 * tx_d < float_d;
+    const bool w = of_w + 0.64 * tx_w < float_w;
+    const bool wj = 10 * us + 0.64 * tx_w + (bx + xb) * 3e-13 < 0.95 * (10 * us + 0.87 * est_w);
+    x.fwd = can_f && (forced >= 0 ? (forced & 1) != 0 : f);
+    x.data = can_d && (forced >= 0 ? (forced & 2) != 0 : d);
+    x.wgt = can_w && (forced >= 0 ? (forced & 4) != 0 : w);
+    x.wgt_joint = can_w && x.data && (forced >= 0 ? (forced & 4) != 0 : w || wj);
+    // beside a weight gradient on the float instructions the staging comes on
+    // top of the mask pass that gradient needs (measured: conv1 at N = 256
+    // 1336 us on the float path, 1401 with the data gradient alone on the
+    // terms); a call for the data gradient alone follows the same rule, so
+    // that both forms of a backward pass give the same bits
+    x.data = x.data && (forced >= 0 || x.wgt_joint ||
+                        of_d + (q.relu ? bt * 2.7e-13 : 0) + 0.76 * tx_d < 0.8 * float_d);
+
+    if (x.fwd) {
+        x.off_wp = align_up(xb, kWsAlign);
+        x.off_fpart = x.off_wp + align_up(wpb, kWsAlign);
+        x.ws_fwd = x.off_fpart + align_up(fpart, kWsAlign);
+    }
+    const bool any_w = x.wgt || x.wgt_joint;
+    if (x.data || any_w) {
+        const int64_t terms = (int64_t)q.N * stage_x3_chunks(q.Wo, x.DHp);
+        x.off_d = any_w ? align_up(xb, kWsAlign) : 0;
+        x.off_sums = x.off_d + align_up(db, kWsAlign);
+        x.off_wt = x.off_sums + align_up(terms * q.K * 4, kWsAlign);
+        x.off_dpart = x.off_wt + (x.data ? align_up(wtb, kWsAlign) : 0);
+        x.off_wpart = x.off_dpart + (x.data ? align_up(dpart, kWsAlign) : 0);
+        x.off_float = x.off_wpart + (any_w ? align_up(wpart, kWsAlign) : 0);
+        x.ws_back = x.off_float + (x.data && x.wgt ? 0 : q.ws_both);
+    }
+}
+
 int plan_conv(const caffe_conv_desc* d, ConvPlan* p)
 {
+    refresh_overrides();
     if (!d)
         return fail(CAFFE_ERR_INVALID_ARG, "desc is NULL");
     if (d->N < 0 || d->C < 1 || d->H < 1 || d->W < 1 || d->K < 1)
@@ -682,21 +947,29 @@ int plan_conv(const caffe_conv_desc* d, ConvPlan* p)
     // Split-K of the forward and data-gradient GEMMs for grids too small to
     // fill the device (small batches, long reductions).
     const int cus = device_cu_count();
-    plan_splits(q.Kg, q.N * q.Ho * q.Wo, q.R, q.fwd_tile, cus, env_tile("CAFFE_CONV_FWD_SPLITS"),
-                &q.fwd_splits, &q.fwd_sps, q.G);
-    plan_splits(q.Mt, (int)dcols, q.Rt, q.dgrad_tile, cus, env_tile("CAFFE_CONV_DGRAD_SPLITS"),
-                &q.dgrad_splits, &q.dgrad_sps, q.G);
+    double est_f = plan_splits(q.Kg, q.N * q.Ho * q.Wo, q.R, q.fwd_tile, cus,
+                               env_tile("CAFFE_CONV_FWD_SPLITS"), &q.fwd_splits, &q.fwd_sps, q.G);
+    double est_d = plan_splits(q.Mt, (int)dcols, q.Rt, q.dgrad_tile, cus,
+                               env_tile("CAFFE_CONV_DGRAD_SPLITS"), &q.dgrad_splits, &q.dgrad_sps,
+                               q.G);
     // tail splits where the grid is not split already
     const int tail_forced = env_tile("CAFFE_CONV_TAIL_SPLITS");
     const int tail_cus = env_tile("CAFFE_CONV_TAIL_UNITS");
     q.fwd_tail = ConvPlan::Tail{0, 1, 0, 0, 0};
     q.dgrad_tail = ConvPlan::Tail{0, 1, 0, 0, 0};
-    if (q.fwd_splits == 1)
-        plan_tail(q.Kg, (int64_t)q.N * q.Ho * q.Wo, q.R, q.fwd_tile, q.G, cus, tail_forced,
-                  tail_cus, &q.fwd_tail);
-    if (q.dgrad_splits == 1)
-        plan_tail(q.Mt, dcols, q.Rt, q.dgrad_tile, q.G, cus, tail_forced, tail_cus,
-                  &q.dgrad_tail);
+    if (q.fwd_splits == 1) {
+        const double t = plan_tail(q.Kg, (int64_t)q.N * q.Ho * q.Wo, q.R, q.fwd_tile, q.G, cus,
+                                   tail_forced, tail_cus, &q.fwd_tail);
+        est_f = q.fwd_tail.splits > 1 ? std::min(est_f, t) : est_f;
+    }
+    if (q.dgrad_splits == 1) {
+        const double t = plan_tail(q.Mt, dcols, q.Rt, q.dgrad_tile, q.G, cus, tail_forced, tail_cus,
+                                   &q.dgrad_tail);
+        est_d = q.dgrad_tail.splits > 1 ? std::min(est_d, t) : est_d;
+    }
+    const double est_w =
+        (double)((tiles * splits + cus - 1) / cus) * cps * 2.0 * wtm * wtn /
+            (0.85 * 157.3e12 / 256) + 8.0 * splits * q.weight_elems / 4e12;
     const int64_t fpart = q.fwd_splits > 1 ? (int64_t)q.fwd_splits * q.top_elems * 4
                                            : q.fwd_tail.bytes;
     const int64_t dpart = q.dgrad_splits > 1
@@ -730,6 +1003,7 @@ int plan_conv(const caffe_conv_desc* d, ConvPlan* p)
     q.off_coltab = q.off_part + align_up(part_bytes, kWsAlign);
     q.ws_weights = q.off_coltab + (q.wgrad_quad ? align_up((size_t)q.ncol_pad * 12, kWsAlign) : 0);
     q.ws_both = std::max(q.ws_data, q.ws_weights);
+    plan_x3(&q, est_f, est_d, est_w);
     return CAFFE_OK;
 }
 
@@ -965,6 +1239,155 @@ int run_weights(const ConvPlan& q, const float* dsrc, const void* bottom, float*
     LAUNCH(launch_wgrad_reduce(part, weight_diff, (int)q.weight_elems, q.splits, sums, bias_diff,
                                q.splits, q.K, accumulate, s),
            "reduce launch");
+    return CAFFE_OK;
+}
+
+// ---- float operands as three bf16 terms
+// A GEMM's launch with its split or tail-split reduce: `reduce` holds what the
+// reduce kernels read of the float path's parameters.
+int run_x3_gemm(GemmX3Params p, int epi, int tile, int splits, int sps, const ConvPlan::Tail& tail,
+                float* part, hipStream_t s)
+{
+    ConvGemmParams r = {};
+    r.M = p.M; r.G = p.G; r.Ncol = p.Ncol; r.OH = p.OH; r.OW = p.OW;
+    r.Cout = p.Cout; r.OutH = p.OutH; r.OutW = p.OutW; r.bias = p.bias; r.relu = p.relu;
+    r.psh = p.psh; r.psw = p.psw; r.a0h = p.a0h; r.a0w = p.a0w; r.oph = p.oph; r.opw = p.opw;
+    r.Cg_out = p.Cg_out;
+    float* out = p.Y;
+    int g0 = 0, c0 = 0, n = splits;
+    if (splits > 1) {
+        GemmX3Params pp = p;
+        pp.Y = part;
+        pp.Y_bytes = nbytes((int64_t)splits * p.G * p.M * p.Ncol, 4);
+        pp.Omask = nullptr;
+        pp.splits = splits;
+        pp.stages_per_split = sps;
+        LAUNCH(launch_conv_gemm_x3(pp, 3, tile, s), "three-term GEMM launch");
+    } else {
+        if (tail.splits > 1) {
+            p.tail_T = tail.T;
+            p.tail_splits = tail.splits;
+            p.tail_sps = tail.sps;
+            p.tail_c0 = tail.c0;
+            p.Pt = part;
+            p.Pt_bytes = nbytes(tail.bytes, 1);
+            g0 = p.G - 1;
+            c0 = tail.c0;
+            n = tail.splits;
+        }
+        LAUNCH(launch_conv_gemm_x3(p, epi, tile, s), "three-term GEMM launch");
+        if (tail.splits <= 1)
+            return CAFFE_OK;
+    }
+    if (epi == 0)
+        LAUNCH(launch_conv_split_reduce_fwd(part, n, r, out, s, g0, c0), "reduce launch");
+    else
+        LAUNCH(launch_conv_split_reduce_dgrad(part, n, r, p.Omask, out, s, g0, c0),
+               "reduce launch");
+    return CAFFE_OK;
+}
+
+int run_forward_x3(const ConvPlan& q, const float* bottom, const float* weight, const float* bias,
+                   float* top, char* ws, hipStream_t s)
+{
+    const ConvPlan::X3& x = q.x3;
+    uint16_t* xh = (uint16_t*)ws;
+    uint16_t* wp = (uint16_t*)(ws + x.off_wp);
+    const int Ctot = q.G * x.Cgp;
+    LAUNCH(launch_stage_x3(bottom, nullptr, xh, nullptr, q.N, q.C, q.H, q.W, q.Cg, x.Cgp, Ctot,
+                           x.XHp, x.XWp, q.ph, q.pw, s),
+           "three-term staging launch");
+    LAUNCH(launch_pack_weights_x3(weight, wp, q.K, q.Cg, x.Cgp, q.kh * q.kw, x.RuF,
+                                  x.Cgp % 32 == 0, s),
+           "three-term weight pack launch");
+    GemmX3Params p = {};
+    p.A = wp;
+    p.X = xh;
+    p.Y = top;
+    p.bias = bias;
+    p.A_bytes = nbytes((int64_t)q.K * x.RuF, 48);
+    p.X_bytes = nbytes((int64_t)q.N * x.XHp * x.XWp * Ctot, 6);
+    p.Y_bytes = nbytes(q.top_elems, 4);
+    p.IHp = x.XHp; p.IWp = x.XWp; p.Ctot = Ctot; p.Cgp = x.Cgp; p.Cg8 = x.Cgp / 8;
+    p.kh = q.kh; p.kw = q.kw; p.ntap = q.kh * q.kw; p.KC = p.ntap * p.Cg8;
+    p.sh = q.sh; p.sw = q.sw;
+    p.OH = q.Ho; p.OW = q.Wo;
+    p.M = q.Kg; p.Ru = x.RuF; p.G = q.G; p.Ncol = q.N * q.Ho * q.Wo;
+    p.relu = q.relu;
+    p.Cout = q.K; p.OutH = q.Ho; p.OutW = q.Wo;
+    p.div_cg8 = make_fastdiv((uint32_t)p.Cg8); p.div_kw = make_fastdiv((uint32_t)p.kw);
+    p.div_ntap = make_fastdiv((uint32_t)p.ntap);
+    p.div_ohw = make_fastdiv((uint32_t)(q.Ho * q.Wo)); p.div_ow = make_fastdiv((uint32_t)q.Wo);
+    p.div_pss = make_fastdiv(1); p.div_psw = make_fastdiv(1);
+    return run_x3_gemm(p, 0, x.fwd_tile, x.fwd_splits, x.fwd_sps, x.fwd_tail,
+                       (float*)(ws + x.off_fpart), s);
+}
+
+int run_data_x3(const ConvPlan& q, const float* bottom_mask, const float* weight,
+                float* bottom_diff, char* ws, hipStream_t s)
+{
+    const ConvPlan::X3& x = q.x3;
+    uint16_t* wt = (uint16_t*)(ws + x.off_wt);
+    const int Ktot = q.G * x.Kgp;
+    LAUNCH(launch_dgrad_weights_x3(weight, wt, q.G, q.Kg, x.Kgp, q.Cg, q.kh, q.kw, q.sh, q.sw,
+                                   q.Th, q.Tw, x.RuD, x.Kgp % 32 == 0, s),
+           "three-term weight transform launch");
+    GemmX3Params p = {};
+    p.A = wt;
+    p.X = (const uint16_t*)(ws + x.off_d);
+    p.Omask = bottom_mask;
+    p.Y = bottom_diff;
+    p.A_bytes = nbytes((int64_t)q.G * q.Mt * x.RuD, 48);
+    p.X_bytes = nbytes((int64_t)q.N * x.DHp * x.DWp * Ktot, 6);
+    p.Y_bytes = nbytes(q.bottom_elems, 4);
+    p.IHp = x.DHp; p.IWp = x.DWp; p.Ctot = Ktot; p.Cgp = x.Kgp; p.Cg8 = x.Kgp / 8;
+    p.kh = q.Th; p.kw = q.Tw; p.ntap = q.Th * q.Tw; p.KC = p.ntap * p.Cg8;
+    p.sh = 1; p.sw = 1; p.oh0 = x.doh0; p.ow0 = x.dow0;
+    p.OH = q.Ah; p.OW = q.Aw;
+    p.M = q.Mt; p.Ru = x.RuD; p.G = q.G; p.Ncol = q.N * q.Ah * q.Aw;
+    p.Cout = q.C; p.OutH = q.H; p.OutW = q.W;
+    p.psh = q.sh; p.psw = q.sw; p.a0h = q.a0h; p.a0w = q.a0w; p.oph = q.ph; p.opw = q.pw;
+    p.Cg_out = q.Cg;
+    p.div_cg8 = make_fastdiv((uint32_t)p.Cg8); p.div_kw = make_fastdiv((uint32_t)p.kw);
+    p.div_ntap = make_fastdiv((uint32_t)p.ntap);
+    p.div_ohw = make_fastdiv((uint32_t)(q.Ah * q.Aw)); p.div_ow = make_fastdiv((uint32_t)q.Aw);
+    p.div_pss = make_fastdiv((uint32_t)(q.sh * q.sw)); p.div_psw = make_fastdiv((uint32_t)q.sw);
+    return run_x3_gemm(p, 1, x.data_tile, x.data_splits, x.data_sps, x.data_tail,
+                       (float*)(ws + x.off_dpart), s);
+}
+
+int run_weights_x3(const ConvPlan& q, const float* bottom, bool kept, float* weight_diff,
+                   int accumulate, char* ws, hipStream_t s)
+{
+    const ConvPlan::X3& x = q.x3;
+    uint16_t* xh = (uint16_t*)ws;
+    float* part = (float*)(ws + x.off_wpart);
+    const int Ctot = q.G * x.Cgp, Ktot = q.G * x.Kgp;
+    if (!kept)
+        LAUNCH(launch_stage_x3(bottom, nullptr, xh, nullptr, q.N, q.C, q.H, q.W, q.Cg, x.Cgp,
+                               Ctot, x.XHp, x.XWp, q.ph, q.pw, s),
+               "three-term staging launch");
+    WgradX3Params p = {};
+    p.D = (const uint16_t*)(ws + x.off_d);
+    p.X = xh;
+    p.P = part;
+    p.D_bytes = nbytes((int64_t)q.N * x.DHp * x.DWp * Ktot, 6);
+    p.X_bytes = nbytes((int64_t)q.N * x.XHp * x.XWp * Ctot, 6);
+    p.P_bytes = nbytes((int64_t)x.splits * q.K * x.Rw, 4);
+    p.IHp = x.XHp; p.IWp = x.XWp; p.Ctot = Ctot; p.Cgp = x.Cgp;
+    p.K = q.K; p.Kg = q.Kg; p.Kgp = x.Kgp; p.Ktot = Ktot;
+    p.DHp = x.DHp; p.DWp = x.DWp; p.dtb = x.dtb; p.dlb = x.dlb;
+    p.kh = q.kh; p.kw = q.kw; p.sh = q.sh; p.sw = q.sw;
+    p.OH = q.Ho; p.OW = q.Wo;
+    p.Rw = x.Rw; p.G = q.G; p.Ncol = q.N * q.Ho * q.Wo;
+    p.cols_per_split = x.cols_per_split;
+    p.splits = x.splits;
+    p.div_ohw = make_fastdiv((uint32_t)(q.Ho * q.Wo));
+    p.div_ow = make_fastdiv((uint32_t)q.Wo);
+    LAUNCH(launch_conv_wgrad_x3(p, x.wgt_tile, s), "three-term weight-gradient launch");
+    LAUNCH(launch_wgrad_reduce_perm(part, weight_diff, q.K, x.Rw, x.Cgp, q.Cg, q.kh, q.kw, q.kw, 1,
+                                    x.splits, accumulate, s),
+           "weight-gradient reduce launch");
     return CAFFE_OK;
 }
 
@@ -1396,6 +1819,51 @@ int backward_bf16_staged(const ConvPlan& q, const float* sums, int terms, bool m
     return CAFFE_OK;
 }
 
+// The float backward with its data gradient (xd) and / or weight gradient (xw)
+// on three bf16 terms: the masked top gradient is staged once for both; a
+// pass that stays on the float instructions runs on `s` as before.  The
+// weight side goes to wst (when given) only if it is the three-term one.
+int backward_x3(const ConvPlan& q, const float* top_diff, const float* top, bool masked,
+                bool mask_bottom, bool kept, const float* bottom, const float* weight, float* bottom_diff,
+                float* weight_diff, float* bias_diff, int accumulate, bool xd, bool xw, char* ws,
+                hipStream_t s, hipStream_t wst)
+{
+    const ConvPlan::X3& x = q.x3;
+    const bool relu = q.relu && !masked;
+    const bool staged_sums = bias_diff && (xw || !weight_diff);
+    float* sums = (float*)(ws + x.off_sums);
+    LAUNCH(launch_stage_x3(top_diff, relu ? top : nullptr, (uint16_t*)(ws + x.off_d),
+                           staged_sums ? sums : nullptr, q.N, q.K, q.Ho, q.Wo, q.Kg, x.Kgp,
+                           q.G * x.Kgp, x.DHp, x.DWp, x.dtb, x.dlb, s),
+           "three-term top-gradient staging launch");
+    const int terms = q.N * stage_x3_chunks(q.Wo, x.DHp);
+    const float* dsrc = top_diff;
+    const bool fd = bottom_diff && !xd, fw = weight_diff && !xw;
+    if (relu && (fd || fw)) {
+        float* D = (float*)(ws + x.off_float + q.off_d);
+        LAUNCH(launch_relu_mask_bias(top_diff, top, D, nullptr, q.N * q.K, q.Ho * q.Wo, 1, s),
+               "ReLU backward launch");
+        dsrc = D;
+    }
+    hipStream_t sw = xw && wst ? wst : s;
+    if (sw != s)
+        CHECK(stream_follow(sw, s));
+    if (xd)
+        CHECK(run_data_x3(q, mask_bottom ? bottom : nullptr, weight, bottom_diff, ws, s));
+    else if (fd)
+        CHECK(run_data(q, dsrc, mask_bottom ? bottom : nullptr, weight, bottom_diff,
+                       ws + x.off_float, s));
+    if (xw)
+        CHECK(run_weights_x3(q, bottom, kept, weight_diff, accumulate, ws, sw));
+    else if (fw)
+        CHECK(run_weights(q, dsrc, bottom, weight_diff, bias_diff, accumulate, ws + x.off_float,
+                          s));
+    if (staged_sums)
+        LAUNCH(launch_bias_reduce(sums, bias_diff, terms, q.K, accumulate, sw),
+               "bias reduce launch");
+    return wst && sw == s ? stream_follow(wst, s) : CAFFE_OK;
+}
+
 // caffe_conv_backward_pool_lrn: the bf16 staging is written by the fused
 // glue backward when a 16-channel block lies in one group; its bias partials
 // (at most one per image, row strip and channel) go after the backward's
@@ -1406,6 +1874,41 @@ size_t pool_lrn_extra(const ConvPlan& q)
 {
     const int64_t elems = pool_lrn_staged(q) ? (int64_t)q.N * q.Ho * q.K : q.top_elems;
     return align_up((size_t)elems * 4, kWsAlign);
+}
+
+// The workspace of a pass: the least, or (preferred) with the three-term
+// staging of the passes that take it.
+int pass_workspace(const ConvPlan& q, int32_t pass, bool preferred, size_t* bytes)
+{
+    if (!bytes)
+        return fail(CAFFE_ERR_INVALID_ARG, "bytes is NULL");
+    const ConvPlan::X3& x = q.x3;
+    size_t least, terms = 0;
+    switch (pass) {
+    case CAFFE_PASS_FORWARD:
+        least = q.ws_fwd;
+        terms = x.ws_fwd;
+        break;
+    case CAFFE_PASS_BACKWARD_DATA:
+        least = q.ws_data;
+        terms = x.data ? x.ws_back : 0;
+        break;
+    case CAFFE_PASS_BACKWARD_WEIGHTS:
+        least = q.ws_weights;
+        terms = x.wgt ? x.ws_back : 0;
+        break;
+    case CAFFE_PASS_BACKWARD:
+        least = q.ws_both;
+        terms = x.ws_back;
+        break;
+    case CAFFE_PASS_BACKWARD_POOL_LRN:
+        least = q.ws_both + pool_lrn_extra(q);
+        break;
+    default:
+        return fail(CAFFE_ERR_INVALID_ARG, "unknown pass %d", pass);
+    }
+    *bytes = preferred ? std::max(least, terms) : least;
+    return CAFFE_OK;
 }
 
 int check_conv_ptrs(const ConvPlan& q, const void* p, bool needed, bool is_blob, const char* name)
@@ -1434,27 +1937,27 @@ int caffe_conv_workspace_size(const caffe_conv_desc* desc, int32_t pass, size_t*
 {
     ConvPlan q;
     CHECK(plan_conv(desc, &q));
-    if (!bytes)
-        return fail(CAFFE_ERR_INVALID_ARG, "bytes is NULL");
-    switch (pass) {
-    case CAFFE_PASS_FORWARD:
-        *bytes = q.ws_fwd;
-        return CAFFE_OK;
-    case CAFFE_PASS_BACKWARD_DATA:
-        *bytes = q.ws_data;
-        return CAFFE_OK;
-    case CAFFE_PASS_BACKWARD_WEIGHTS:
-        *bytes = q.ws_weights;
-        return CAFFE_OK;
-    case CAFFE_PASS_BACKWARD:
-        *bytes = q.ws_both;
-        return CAFFE_OK;
-    case CAFFE_PASS_BACKWARD_POOL_LRN:
-        *bytes = q.ws_both + pool_lrn_extra(q);
-        return CAFFE_OK;
-    default:
-        return fail(CAFFE_ERR_INVALID_ARG, "unknown pass %d", pass);
-    }
+    return pass_workspace(q, pass, false, bytes);
+}
+
+int caffe_conv_workspace_preferred(const caffe_conv_desc* desc, int32_t pass, size_t* bytes)
+{
+    ConvPlan q;
+    CHECK(plan_conv(desc, &q));
+    return pass_workspace(q, pass, true, bytes);
+}
+
+int caffe_conv_uses_terms(const caffe_conv_desc* desc, int32_t pass)
+{
+    ConvPlan q;
+    if (plan_conv(desc, &q) != CAFFE_OK)
+        return 0;
+    const ConvPlan::X3& x = q.x3;
+    return pass == CAFFE_PASS_FORWARD            ? x.fwd
+           : pass == CAFFE_PASS_BACKWARD_DATA    ? x.data
+           : pass == CAFFE_PASS_BACKWARD_WEIGHTS ? x.wgt
+           : pass == CAFFE_PASS_BACKWARD         ? x.data && x.wgt_joint
+                                                 : 0;
 }
 
 int caffe_conv_forward(const caffe_conv_desc* desc, const void* bottom, const void* weight,
@@ -1486,6 +1989,9 @@ int caffe_conv_forward_ex(const caffe_conv_desc* desc, const void* bottom, const
     if (q.dense)
         return run_dense_forward(q, (const float*)bottom, (const float*)weight, bias, top,
                                  (char*)workspace, (hipStream_t)stream);
+    if (q.x3.fwd && ws_bytes >= q.x3.ws_fwd)
+        return run_forward_x3(q, (const float*)bottom, (const float*)weight, bias, top,
+                              (char*)workspace, (hipStream_t)stream);
     return run_forward(q, bottom, weight, bias, top, (char*)workspace, (hipStream_t)stream);
 }
 
@@ -1556,7 +2062,8 @@ int backward_impl(const caffe_conv_desc* desc, const float* top_diff, const floa
     if (accumulate != 0 && accumulate != 1)
         return fail(CAFFE_ERR_INVALID_ARG, "accumulate must be 0 or 1");
     if (flags & ~(CAFFE_BACKWARD_TOP_DIFF_MASKED | CAFFE_BACKWARD_MASK_BOTTOM_DIFF |
-                  CAFFE_BACKWARD_BOTTOM_STAGED | CAFFE_BACKWARD_TOP_STAGED))
+                  CAFFE_BACKWARD_BOTTOM_STAGED | CAFFE_BACKWARD_TOP_STAGED |
+                  CAFFE_BACKWARD_BOTTOM_TERMS))
         return fail(CAFFE_ERR_INVALID_ARG, "unknown backward flags 0x%x", flags);
     const bool staged = (flags & CAFFE_BACKWARD_BOTTOM_STAGED) != 0;
     const bool top_staged = (flags & CAFFE_BACKWARD_TOP_STAGED) != 0;
@@ -1613,6 +2120,17 @@ int backward_impl(const caffe_conv_desc* desc, const float* top_diff, const floa
                              (const float*)weight, bottom_diff, weight_diff, bias_diff,
                              accumulate, ws, s));
         return wst ? stream_follow(wst, s) : CAFFE_OK;
+    }
+    const bool x3_ws = ws_bytes >= q.x3.ws_back;
+    const bool xd = q.x3.data && bottom_diff && x3_ws;
+    const bool xw = (q.x3.wgt || (xd && q.x3.wgt_joint)) && weight_diff && x3_ws;
+    if (xd || xw) {
+        // the forward's staging of bottom, where it ran on this workspace
+        const bool kept = (flags & CAFFE_BACKWARD_BOTTOM_TERMS) != 0 && q.x3.fwd &&
+                          ws_bytes >= q.x3.ws_fwd;
+        return backward_x3(q, top_diff, top, masked, mask_bottom, kept, (const float*)bottom,
+                           (const float*)weight, bottom_diff, weight_diff, bias_diff, accumulate,
+                           xd, xw, ws, s, wst);
     }
     const float* dsrc = top_diff;
     if (q.relu && !masked && (bottom_diff || weight_diff) && q.top_elems > 0) {

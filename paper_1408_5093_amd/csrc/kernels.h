@@ -386,6 +386,78 @@ hipError_t launch_dgrad_weights_bf16(const uint16_t* W, uint16_t* Wt, int G, int
                                      int Cg, int kh, int kw, int sh, int sw, int Th, int Tw,
                                      int Rtp, int blocked, hipStream_t s);
 
+// ---- float operands as three bf16 terms (conv_triple.hip) ----
+// Units of 8 channels x 3 terms (48 bytes): X[N][IHp][IWp][Ctot / 8][3][8]
+// zero-bordered, A[G*M][Ru][3][8] (Ru a whole number of 4-unit stages).
+//   C_g[m][col] = sum over the kh x kw taps and the group's Cgp channels
+// as in GemmBf16Params.  The reduction runs over units kc = tap * Cg8 + c8,
+// or, where Cgp is a multiple of 32, in 32-channel blocks outer, taps inner:
+// unit ((c8 / 4) * ntap + tap) * 4 + c8 % 4.  Epilogues as ConvGemmParams:
+// epi 0 forward, epi 1 phase-stacked data gradient (Omask: a float tensor
+// like Y), each with a tail split; epi 3 split-K partials.
+struct GemmX3Params {
+    const uint16_t* A;
+    const uint16_t* X;
+    const float* Omask;
+    float* Y;
+    const float* bias;
+    uint32_t A_bytes, X_bytes, Y_bytes;
+    int IHp, IWp, Ctot, Cgp, Cg8, KC;
+    int kh, kw, ntap, sh, sw, oh0, ow0;
+    int OH, OW;
+    int M, Ru, G, Ncol;
+    int relu;
+    int Cout, OutH, OutW;
+    int psh, psw, a0h, a0w, oph, opw, Cg_out;
+    FastDiv div_cg8, div_kw, div_ntap, div_ohw, div_ow, div_pss, div_psw;
+    int splits, stages_per_split;
+    int tail_T, tail_splits, tail_sps, tail_c0;
+    float* Pt;
+    uint32_t Pt_bytes;
+};
+enum X3Tile {
+    X3TILE_128x256 = 0,  // 32x32x16 MFMA, 8 waves as 2 x 4, each 64x64
+    X3TILE_96x256 = 1,   // 32x32x16, 8 waves as 1 x 8, each 96x32
+    X3TILE_64x256 = 2,   // 32x32x16, 8 waves as 1 x 8, each 64x32
+    X3TILE_48x128 = 3,   // 16x16x32, 4 waves as 1 x 4, each 48x32, two workgroups per unit
+    X3TILE_COUNT
+};
+constexpr int kX3TK = 32;  // channels per stage
+int x3_tile_m(int tile);
+int x3_tile_n(int tile);
+hipError_t launch_conv_gemm_x3(const GemmX3Params& p, int epi, int tile, hipStream_t s);
+// Split-K weight gradient over two x3 stagings (D [N][DHp][DWp][Ktot], real
+// pixels at (dtb, dlb); X as in GemmX3Params): the sums and partials
+// P[split][g*Kg + m][(u*kw + v)*Cgp + c] of WgradBf16Params.
+struct WgradX3Params {
+    const uint16_t* D;
+    const uint16_t* X;
+    float* P;
+    uint32_t D_bytes, X_bytes, P_bytes;
+    int IHp, IWp, Ctot, Cgp, K, Kg, Kgp, Ktot;
+    int DHp, DWp, dtb, dlb;
+    int kh, kw, sh, sw;
+    int OH, OW;
+    int Rw, G;
+    int Ncol, cols_per_split, splits;  // cols_per_split: whole 32-pixel stages
+    FastDiv div_ohw, div_ow;
+};
+enum X3WgradTile { X3WTILE_128x256 = 0, X3WTILE_96x256 = 1, X3WTILE_64x256 = 2, X3WTILE_COUNT };
+int x3_wgrad_tile_m(int tile);
+hipError_t launch_conv_wgrad_x3(const WgradX3Params& p, int tile, hipStream_t s);
+// Staging of a float blob X[n][C][H][W] (with Y non-null, X [Y > 0]); sums
+// (may be null): per channel the partial sums of the staged floats,
+// sums[c * T + t], T = N * stage_x3_chunks(W, Hp).  W <= 256.
+int stage_x3_chunks(int W, int Hp);
+hipError_t launch_stage_x3(const float* X, const float* Y, uint16_t* Xp, float* sums, int N, int C,
+                           int H, int W, int Cg, int Cgp, int Ctot, int Hp, int Wp, int tb, int lb,
+                           hipStream_t s);
+hipError_t launch_pack_weights_x3(const float* W, uint16_t* Wp, int K, int Cg, int Cgp, int khw,
+                                  int Ru, int blocked, hipStream_t s);
+hipError_t launch_dgrad_weights_x3(const float* W, uint16_t* Wt, int G, int Kg, int Kgp, int Cg,
+                                   int kh, int kw, int sh, int sw, int Th, int Tw, int Ru,
+                                   int blocked, hipStream_t s);
+
 // D = relu ? G * [Y > 0] : G (written to D unless D is null) and, unless
 // plane_sums is null, plane_sums[p] = sum of D over plane p (fixed order).
 hipError_t launch_relu_mask_bias(const float* G, const float* Y, float* D, float* plane_sums,

@@ -13,16 +13,18 @@ call; this module only owns buffers and the call order.
 """
 import torch
 
-from . import (BACKWARD_BOTTOM_STAGED, BACKWARD_MASK_BOTTOM_DIFF, BACKWARD_POOL_MASK_OFFSETS,
+from . import (BACKWARD_BOTTOM_STAGED, BACKWARD_BOTTOM_TERMS, BACKWARD_MASK_BOTTOM_DIFF,
+               BACKWARD_POOL_MASK_OFFSETS,
                BACKWARD_TOP_DIFF_MASKED,
                BACKWARD_TOP_STAGED, CAFFE_BF16_F32_BOTTOM, CAFFE_F32, FORWARD_BOTTOM_STAGED,
                caffe_conv_backward_into, conv_stage_below_supported, pool_lrn_stage_supported,
-               PASS_BACKWARD, PASS_BACKWARD_POOL_LRN, PASS_BACKWARD_WEIGHTS, PASS_FORWARD,
+               PASS_BACKWARD, PASS_BACKWARD_DATA, PASS_BACKWARD_POOL_LRN, PASS_BACKWARD_WEIGHTS,
+               PASS_FORWARD,
                POOL_LRN_STAGE_ONLY, POOL_MASK_OFFSETS, POOL_RELU_INPUT, Workspace,
                caffe_conv_backward,
                caffe_conv_backward_pool_lrn,
                caffe_conv_forward, conv_desc, conv_out_shape, lrn_desc,
-               conv_workspace_size, lrn_backward, lrn_forward, maxpool_backward, maxpool_forward,
+               conv_uses_terms, conv_workspace_preferred, conv_workspace_size, lrn_backward, lrn_forward, maxpool_backward, maxpool_forward,
                lrn_pool_backward, pool_desc, pool_lrn_forward, pool_lrn_supported, relu_backward,
                pool_out_shape, sgd_learning_rate, sgd_update, softmax_loss)
 
@@ -53,6 +55,7 @@ class ConvStack:
         ws_need = 0
         ws_layer = []
         ws_weights = 0
+        self.terms = []  # layers whose gradients run on three-term operands (float)
         for l, L in enumerate(self.layers):
             d = conv_desc((N, L.C, L.H, L.W), (L.K, L.C // L.g, L.k, L.k), L.s, L.p, L.g, L.relu,
                           dt)
@@ -69,8 +72,21 @@ class ConvStack:
             glue_l = [kind for kind, _ in self.glue.get(l, [])]
             if bf16 and fuse_staging and glue_l == ["pool", "lrn"]:
                 need_l = max(need_l, conv_workspace_size(d, PASS_BACKWARD_POOL_LRN))
-            ws_need = max(ws_need, need_l)
-            ws_layer.append(need_l)
+            # float layers on three-term operands get a workspace of their own:
+            # the forward's staging of the input stays there for the backward,
+            # and the weight side may run beside the next layers
+            uses = [not bf16 and conv_uses_terms(d, p) for p in
+                    (PASS_FORWARD, PASS_BACKWARD_DATA, PASS_BACKWARD_WEIGHTS, PASS_BACKWARD)]
+            own = any(uses)
+            # (without, with the data gradient)
+            self.terms.append((uses[2], uses[2] or uses[3]))
+            if own:
+                need_l = max(need_l, conv_workspace_preferred(d, PASS_BACKWARD),
+                             conv_workspace_preferred(d, PASS_FORWARD))
+            own = own or bf16
+            if not own:
+                ws_need = max(ws_need, need_l)
+            ws_layer.append((need_l, own))
             ws_weights = max(ws_weights, conv_workspace_size(d, PASS_BACKWARD_WEIGHTS))
             cur = (N, L.K, Ho, Wo)
             stages = []
@@ -93,14 +109,12 @@ class ConvStack:
                 flat = nx.H == 1 and nx.W == 1 and cur[1] * cur[2] * cur[3] == nx.C
                 if cur != (N, nx.C, nx.H, nx.W) and not flat:
                     raise ValueError(f"layer {l} output {cur} does not feed layer {l + 1}")
-        # bf16: a workspace per layer, so that its backward reads the input
-        # its forward staged there (BACKWARD_BOTTOM_STAGED); fp32 stages
-        # nothing and all layers share one
-        if bf16:
-            self.ws_of = [Workspace(dev).get(n) for n in ws_layer]
-        else:
-            self.ws = Workspace(dev).get(ws_need)
-            self.ws_of = [self.ws] * len(ws_layer)
+        # a workspace per layer that stages its operands (bf16, and float on
+        # three-term operands), so that its backward reads the input its
+        # forward staged there (BACKWARD_BOTTOM_STAGED, BACKWARD_BOTTOM_TERMS);
+        # the layers that stage nothing share one
+        shared = Workspace(dev).get(ws_need)
+        self.ws_of = [Workspace(dev).get(n) if own else shared for n, own in ws_layer]
         # fp32 backward: a layer whose top gradient arrives masked runs its
         # weight and bias gradients on a side stream (default priority, own
         # workspace) while the data gradient and the glue below it go on in
@@ -159,7 +173,8 @@ class ConvStack:
         # masked top gradients of the layers whose ReLU backward runs as its
         # own pass (split backward only)
         self.dtop_relu = [torch.empty_like(self.top[l])
-                          if self.split_backward and L.relu and not self.top_masked[l] else None
+                          if (self.split_backward and L.relu and not self.top_masked[l] and
+                              not all(self.terms[l])) else None
                           for l, L in enumerate(self.layers)]
         # A max-pool directly followed by an LRN runs as one fused pass each
         # way (the pooled gradient never stored) when the kernels take the
@@ -313,6 +328,21 @@ class ConvStack:
             if self.bf16:
                 flags |= BACKWARD_BOTTOM_STAGED
             top = self.top[l] if L.relu else None
+            if self.terms[l][want_dx]:
+                flags |= BACKWARD_BOTTOM_TERMS
+                # one call: the masked top gradient is staged once for both
+                # gradients, the weight side then runs on the side stream
+                tag = "both" if want_dx else "wgt"
+                side = self.side if split and not self.serial else None
+                self._mark((tag, l, "begin"), s)
+                caffe_conv_backward(self.descs[l], g, top, bottom, self.W[l],
+                                    self.dbottom[l] if want_dx else None, self.dW[l], self.db[l],
+                                    0, flags, self.ws_of[l], s, weight_stream=side)
+                self._mark((tag, l, "end"), s)
+                if side is not None:
+                    self._mark((tag, l, "end"), side)
+                g = self.dbottom[l]
+                continue
             if split and self.dtop_relu[l] is not None:
                 g = relu_backward(self.top[l], g, out=self.dtop_relu[l], stream=s)
                 flags |= BACKWARD_TOP_DIFF_MASKED

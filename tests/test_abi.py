@@ -383,3 +383,37 @@ def test_solver_argument_checks():
         cc.sgd_learning_rate("fixed", 0.01, -1)
     with pytest.raises(cc.CaffeError):
         cc.sgd_learning_rate("inv", 0.01, 2, gamma=-1.0, power=0.75)  # (1 - 2)^-0.75
+
+
+def test_workspace_preferred_holds_the_terms():
+    """A pass that runs on three-term operands asks for room for its staging
+    (48 bytes per 8 channels and bordered pixel), its packed weights and, in
+    the backward pass, both gradients' staging; any other pass for the least."""
+    import random
+    rng = random.Random(1408)
+
+    def up(v, a):
+        return (v + a - 1) // a * a
+
+    took = [0, 0, 0]
+    for _ in range(3000):
+        g, k, s = rng.choice((1, 2, 3)), rng.choice((1, 2, 3, 5, 7)), rng.choice((1, 1, 2, 3))
+        N, Cg, Kg = rng.randint(1, 256), rng.randint(1, 128), rng.randint(1, 160)
+        H, W, p = rng.randint(7, 60), rng.randint(7, 80), rng.randint(0, 3)
+        d = cc.conv_desc((N, g * Cg, H, W), (g * Kg, Cg, k, k), s, p, g, rng.random() < 0.5)
+        Ho, Wo = cc.conv_out_shape(d)
+        xb = N * max(H + p, (Ho - 1) * s + k) * max(W + p, (Wo - 1) * s + k) * g * up(Cg, 8) * 6
+        db = N * Ho * Wo * g * up(Kg, 8) * 6
+        wp = g * Kg * up(k * k * up(Cg, 8) // 8, 4) * 48
+        for i, (pas, need) in enumerate(((cc.PASS_FORWARD, xb + wp), (cc.PASS_BACKWARD_DATA, db),
+                                         (cc.PASS_BACKWARD_WEIGHTS, xb + db))):
+            least, best = cc.conv_workspace_size(d, pas), cc.conv_workspace_preferred(d, pas)
+            assert best >= least
+            if cc.conv_uses_terms(d, pas):
+                took[i] += 1
+                assert best >= need, (pas, best, need)
+            else:
+                assert best == least
+        if cc.conv_uses_terms(d, cc.PASS_BACKWARD):
+            assert cc.conv_workspace_preferred(d, cc.PASS_BACKWARD) >= xb + db
+    assert min(took) > 100, took

@@ -1,0 +1,169 @@
+"""Float convolutions on three bf16 terms (conv_triple.hip) against the CPU
+oracle and against the float kernels.
+
+Bound.  The products of the first terms add up in a float accumulator that is
+rounded once per 16 reduction elements (32 in the 16-row tiles), the small ones
+in another; the splits' partials and the bias add a few roundings more.  For
+operands of random sign these roundings are independent and the running sum is
+at most the result's size in the mean, so the 2-norm error is about
+2^-24 sqrt(R / 16) of the result's norm plus the last rounding.  A missing
+product of any order (2^-9, 2^-18 of a term) is above it.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1408_5093_amd as cc
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).to(DEV)
+
+
+def _close(got, ref, R, what):
+    torch.cuda.synchronize()
+    got = got.double().cpu().numpy()
+    assert got.shape == ref.shape and np.all(np.isfinite(got)), what
+    rel = np.linalg.norm(got - ref) / max(np.linalg.norm(ref), 1e-300)
+    bound = (2 + np.sqrt(R / 16)) * 2.0 ** -24
+    assert rel <= bound, f"{what}: {rel:.2e} > {bound:.2e}"
+
+
+def _case(c, seed=0):
+    N, C, H, W, K, kh, kw, sh, sw, ph, pw, g = c
+    rng = np.random.default_rng([1408, seed] + list(c))
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    w = (rng.standard_normal((K, C // g, kh, kw)) * 0.3).astype(np.float32)
+    b = rng.standard_normal(K).astype(np.float32)
+    Ho, Wo = (H + 2 * ph - kh) // sh + 1, (W + 2 * pw - kw) // sw + 1
+    gd = rng.standard_normal((N, K, Ho, Wo)).astype(np.float32)
+    top = np.maximum(rng.standard_normal(gd.shape), 0).astype(np.float32)
+    return x, w, b, gd, top
+
+
+# N, C, H, W, K, kh, kw, sh, sw, ph, pw, group
+CASES = [
+    (1, 8, 5, 5, 8, 3, 3, 1, 1, 1, 1, 1),       # one ragged tile, one unit per tap
+    (2, 5, 9, 7, 13, 3, 2, 1, 1, 1, 0, 1),      # padded channels both ways
+    (3, 32, 13, 13, 64, 3, 3, 1, 1, 1, 1, 1),   # whole 32-channel stages
+    (2, 96, 15, 11, 96, 5, 5, 1, 1, 2, 2, 2),   # 48 channels per group: half stages
+    (2, 40, 12, 9, 130, 3, 3, 2, 2, 1, 1, 1),   # strided, rows past a 128-row tile
+    (1, 64, 20, 17, 192, 1, 1, 1, 1, 0, 0, 1),  # 1x1, 96-row tiles
+    (2, 16, 19, 23, 48, 7, 5, 3, 2, 3, 1, 2),   # unequal strides, phase-stacked rows
+    (1, 24, 3, 256, 20, 1, 3, 1, 1, 0, 1, 1),   # rows of 256 pixels, the staging's limit
+    (2, 8, 6, 6, 9, 2, 2, 3, 3, 0, 0, 1),       # stride past the kernel: unread pixels
+    (5, 12, 4, 4, 24, 4, 4, 1, 1, 3, 3, 3),     # pad wider than the image's margin
+]
+
+
+@pytest.mark.parametrize("c", CASES)
+@pytest.mark.parametrize("relu", [False, True])
+def test_terms_parity(overrides, c, relu):
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    N, C, H, W, K, kh, kw, sh, sw, ph, pw, g = c
+    x, w, b, gd, top = _case(c)
+    R = (C // g) * kh * kw
+    y = cc.conv_forward(_t(x), _t(w), _t(b), (sh, sw), (ph, pw), g, relu)
+    _close(y, oracle.conv_forward(x, w, b, (sh, sw), (ph, pw), g, relu), R, "forward")
+    dx, dw, db = cc.conv_backward(_t(x), _t(w), _t(gd), _t(top), (sh, sw), (ph, pw), g, relu)
+    rx, rw, rb = oracle.conv_backward(x, w, gd, top=top, stride=(sh, sw), pad=(ph, pw), group=g,
+                                      relu=relu)
+    _close(dx, rx, (K // g) * kh * kw, "data gradient")
+    _close(dw, rw, gd.size // K, "weight gradient")
+    _close(db, rb, gd.size // K, "bias gradient")
+
+
+@pytest.mark.parametrize("tile", range(4))
+@pytest.mark.parametrize("how", [{"SPLITS": 3}, {"TAIL_SPLITS": 2, "TAIL_UNITS": 3}])
+def test_terms_tiles_and_splits(overrides, tile, how):
+    """Every tile with an even split and with a tail split of its reduction."""
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    overrides.setenv("CAFFE_X3_FWD_TILE", str(tile))
+    overrides.setenv("CAFFE_X3_DGRAD_TILE", str(tile))
+    overrides.setenv("CAFFE_X3_WGRAD_TILE", str(min(tile, 2)))
+    if "SPLITS" in how:
+        for k in ("FWD", "DGRAD", "WGRAD"):
+            overrides.setenv(f"CAFFE_X3_{k}_SPLITS", str(how["SPLITS"]))
+    else:
+        for k, v in how.items():
+            overrides.setenv(f"CAFFE_X3_{k}", str(v))
+    c = (3, 64, 21, 19, 140, 3, 3, 1, 1, 1, 1, 2)
+    N, C, H, W, K, kh, kw, sh, sw, ph, pw, g = c
+    x, w, b, gd, top = _case(c)
+    y = cc.conv_forward(_t(x), _t(w), _t(b), 1, 1, g, True)
+    _close(y, oracle.conv_forward(x, w, b, 1, 1, g, True), 32 * 9, "forward")
+    xs = np.abs(x) * (x > -0.5)
+    dx, dw, _ = cc.conv_backward(_t(xs), _t(w), _t(gd), _t(top), 1, 1, g, True,
+                                 flags=cc.BACKWARD_MASK_BOTTOM_DIFF)
+    rx, rw, _ = oracle.conv_backward(xs, w, gd, top=top, stride=1, pad=1, group=g, relu=True)
+    _close(dx, rx * (xs > 0), 70 * 9, "masked data gradient")
+    _close(dw, rw, N * H * W, "weight gradient")
+
+
+def test_terms_non_finite_as_float(overrides):
+    """Infinities, NaN and the largest floats give what the float kernels
+    give, element by element."""
+    c = (2, 48, 11, 12, 40, 3, 3, 1, 1, 1, 1, 2)
+    x, w, b, gd, top = _case(c)
+    x[0, 3, 2, 5], x[0, 30, 9, 9], x[1, 4, 4, 4] = np.inf, -np.inf, np.nan
+    x[1, 7, 10, 0], x[0, 9, 0, 0] = 3.4e38, 0.0
+    w[3, 2, 1, 1], w[21, 5, 0, 0], w[30, 1, 2, 2] = np.inf, -np.inf, np.nan
+    w[4] *= 1e-30
+    w[5, :, 1, 1] = 1.0
+    gd[0, 11, 3, 3], gd[1, 25, 0, 0], gd[1, 2, 5, 5] = np.inf, -np.inf, np.nan
+    outs = []
+    for mode in ("0", "7"):
+        overrides.setenv("CAFFE_CONV_X3", mode)
+        with np.errstate(all="ignore"):
+            y = cc.conv_forward(_t(x), _t(w), _t(b), 1, 1, 2, False)
+            outs.append([y] + list(cc.conv_backward(_t(x), _t(w), _t(gd), None, 1, 1, 2, False)))
+    torch.cuda.synchronize()
+    for a, t in zip(*outs):
+        assert torch.equal(torch.isnan(a), torch.isnan(t))
+        assert torch.equal(torch.isposinf(a), torch.isposinf(t))
+        assert torch.equal(torch.isneginf(a), torch.isneginf(t))
+        f = torch.isfinite(a)
+        assert f.any()
+        scale = a[f].abs().clamp_min(1e-3)
+        assert ((a[f] - t[f]).abs() / scale).max() < 1e-3
+
+
+def test_terms_kept_bottom_and_weight_stream(overrides):
+    """The forward's staging read by the backward, and the weight side on a
+    stream of its own, give the same bits; a workspace of the minimum size
+    takes the float kernels."""
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    c = (4, 32, 14, 13, 72, 5, 5, 1, 1, 2, 2, 1)
+    x, w, b, gd, top = (_t(a) for a in _case(c))
+    d = cc.conv_desc(x.shape, w.shape, 1, 2, 1, True)
+    passes = (cc.PASS_FORWARD, cc.PASS_BACKWARD)
+    need = max(cc.conv_workspace_preferred(d, p) for p in passes)
+    assert all(cc.conv_workspace_preferred(d, p) > cc.conv_workspace_size(d, p) for p in passes)
+    assert cc.conv_uses_terms(d, cc.PASS_BACKWARD)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device=DEV)
+    side = torch.cuda.Stream()
+
+    def run(buf, flags=0, stream=None, kept=False, fwd=None):
+        y = torch.empty_like(gd)
+        o = [torch.empty_like(x), torch.empty_like(w), torch.empty_like(b)]
+        cc.caffe_conv_forward(d, x, w, b, y, buf if fwd is None else fwd)
+        if not kept:
+            buf.fill_(0xFF)
+        cc.caffe_conv_backward(d, gd, top, x, w, *o, 0, flags, buf, weight_stream=stream)
+        torch.cuda.synchronize()
+        return [y] + o
+
+    ref = run(ws)
+    for got in (run(ws, cc.BACKWARD_BOTTOM_TERMS, None, True), run(ws, 0, side),
+                run(ws, cc.BACKWARD_BOTTOM_TERMS, side, True)):
+        assert all(torch.equal(a, t) for a, t in zip(ref, got))
+    least = [torch.empty(cc.conv_workspace_size(d, p), dtype=torch.uint8, device=DEV)
+             for p in (cc.PASS_BACKWARD, cc.PASS_FORWARD)]
+    got = run(least[0], cc.BACKWARD_BOTTOM_TERMS, None, True, least[1])  # (no effect there)
+    overrides.setenv("CAFFE_CONV_X3", "0")
+    assert all(torch.equal(a, t) for a, t in zip(run(least[0], fwd=least[1]), got))
