@@ -69,7 +69,7 @@ struct ConvPlan {
     int fwd_rpad;
     size_t off_taps_fwd;
     int blocked, xcd_order, wgrad_xcd_order;  // reduction and tile orders (see kernels.h)
-    bool wgrad_unit_order;                    // bf16 weight gradient: units per XCD
+    bool wgrad_unit_order;                    // float weight gradient: units per XCD
     int dgrad_blocked;                        // bf16 data gradient: channel-blocked order
     // workspace layout (byte offsets), per pass
     size_t off_d, off_sums, off_wt, off_part;
@@ -535,27 +535,34 @@ int plan_bf16(ConvPlan* p)
     q.wgrad_tile = pick_bf16_wgrad_tile(q.Kg, env_tile("CAFFE_BF16_WGRAD_TILE"));
     const int wtm = bf16_wgrad_tile_m(q.wgrad_tile), wtn = kBf16WgradTN;
     const int64_t tiles = (int64_t)((q.Kg + wtm - 1) / wtm) * ((q.Rw + wtn - 1) / wtn) * q.G;
-    // one workgroup per compute unit at a time (its LDS): about two rounds
-    const int64_t target = env_tile("CAFFE_CONV_WGRAD_BLOCKS") > 0
-                               ? env_tile("CAFFE_CONV_WGRAD_BLOCKS")
-                               : 2 * (int64_t)device_cu_count();
+    // One workgroup per compute unit at a time (its LDS).  About two rounds of
+    // the units would be `target`; of the split counts from as many
+    // as fit those two rounds on, the one with the least modelled time: whole rounds times the
+    // stages of a split, plus the partials written and read once.  (At exactly
+    // target conv2's 520 workgroups took a third round for eight of them.)
+    const int forced = env_tile("CAFFE_CONV_WGRAD_BLOCKS");
+    const int64_t cus = std::max(1, device_cu_count());
+    const int64_t target = forced > 0 ? forced : 2 * cus;
     int64_t splits = (target + tiles - 1) / tiles;
-    const int64_t max_splits = std::max<int64_t>(1, ncol / (8 * tk));
-    const int64_t max_by_bytes = std::max<int64_t>(1, kMaxTensorBytes / (rw * q.K * 4));
-    // Unit order (see WgradBf16Params::unit_order) where a (group, split)
-    // unit holds at least 7 tiles: measured on the CaffeNet layers at N=512,
-    // each unit's slab then comes from HBM once instead of once per tile
-    // (conv3-5: 4-6x fewer bytes); with fewer tiles per unit (conv1, conv2)
-    // the linear order was as fast or faster.  The split count then becomes
-    // a multiple of 8 / gcd(G, 8), so that every XCD takes as many units.
-    const int64_t per_unit = tiles / q.G;
-    const int uo = env_tile("CAFFE_BF16_WGRAD_UNIT_ORDER");
-    q.wgrad_unit_order = uo >= 0 ? uo != 0 : per_unit >= 7;
-    if (q.wgrad_unit_order) {
-        const int64_t m = q.G % 8 == 0 ? 1 : q.G % 4 == 0 ? 2 : q.G % 2 == 0 ? 4 : 8;
-        splits = std::max<int64_t>(m, (splits + m / 2) / m * m);
+    const int64_t max_splits = std::max<int64_t>(
+        1, std::min(ncol / (8 * tk), kMaxTensorBytes / (rw * q.K * 4)));
+    if (forced <= 0) {
+        const double t_stage = 2.0 * wtm * wtn * tk / (1.0e15 / 256);
+        double best = 1e30;
+        const int64_t lo = std::max<int64_t>(1, std::min(max_splits, target / tiles));
+        const int64_t hi = std::max(lo, std::min(max_splits, 2 * splits));
+        for (int64_t sp = lo; sp <= hi; ++sp) {
+            const int64_t rounds = (tiles * sp + cus - 1) / cus;
+            const int64_t nst = ((ncol + sp - 1) / sp + tk - 1) / tk;
+            const double t = rounds * (nst + 5) * t_stage + 8.0 * sp * rw * q.K / 4e12;
+            if (t < best) {
+                best = t;
+                splits = sp;
+            }
+        }
     }
-    splits = std::max<int64_t>(1, std::min(std::min(splits, max_splits), max_by_bytes));
+    q.wgrad_xcd_order = env_tile("CAFFE_BF16_WGRAD_UNIT_ORDER") != 0;
+    splits = std::max<int64_t>(1, std::min(splits, max_splits));
     int64_t cps = (ncol + splits - 1) / splits;
     cps = std::max<int64_t>(tk, (cps + tk - 1) / tk * tk);
     splits = std::max<int64_t>(1, (ncol + cps - 1) / cps);
@@ -1641,7 +1648,7 @@ int run_weights_bf16(const ConvPlan& q, const uint16_t* dh, const void* bottom, 
     p.splits = q.splits;
     p.div_ohw = make_fastdiv((uint32_t)(q.Ho * q.Wo));
     p.div_ow = make_fastdiv((uint32_t)q.Wo);
-    p.unit_order = q.wgrad_unit_order ? 1 : 0;
+    p.xcd_order = q.wgrad_xcd_order;
     LAUNCH(launch_conv_wgrad_bf16(p, q.wgrad_tile, s), "bf16 weight-gradient launch");
     LAUNCH(launch_wgrad_reduce_perm(part, weight_diff, q.K, q.Rw, q.Cgp, q.Cg, q.kh, q.kw, q.kwp,
                                     q.s2d ? q.s2d : 1, q.splits, accumulate, s),

@@ -87,11 +87,22 @@ __device__ __forceinline__ void copy16_lds(__amdgpu_buffer_rsrc_t r, u32x4* dst,
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, voff, soff, 0, 0);
 }
 
-// Slot permutation of the 8 chunks of tile row r (bits 0..3 of r only).
+// Slot permutation of the 8 chunks of tile row r (bits 1..3 of r only).  The
+// LDS serves a 16-byte read in groups of 16 lanes (0-3, 12-15, 20-23, 24-27 and
+// 4-7, 8-11, 16-19, 28-31 of each half wave), two rows of 128 bytes cover its
+// 64 banks: in the 32-row form a group reads one chunk of eight rows of each
+// parity, in the 16-row form one chunk of rows 0-3 and 12-15 and the next one
+// of rows 4-11.  This order keeps both apart (the one before, r & 6 with bit 0
+// from bits 0 and 3, lost half the 16-row form's LDS cycles to conflicts).
 __device__ __forceinline__ int chunk_swz(int r)
 {
-    return (r & 6) | ((r ^ (r >> 3)) & 1);
+    return ((((r >> 2) ^ (r >> 3)) & 1) << 2) | (r & 2) | ((r >> 3) & 1);
 }
+// The same for the weight gradient's [pixel][64 channels] tile: a transposed
+// read takes four chunks of four consecutive pixels at once, so the upper two
+// of each four pixels swap the halves of their line (chunk_swz in its place:
+// half the LDS cycles were conflicts).
+__device__ __forceinline__ int pixel_swz(int k) { return ((k >> 1) & 1) << 2; }
 
 // Workgroup barrier between pipeline stages.  Each wave has already waited
 // (vmcnt) for its own copies of the stage it is about to read, and its reads
@@ -547,7 +558,7 @@ conv_gemm_bf16_kernel(const GemmBf16Params p)
 // tile's 128 output channels, one of the X tile the tile's TN reduction
 // indices r = (u, v, c) (8 channels of one tap per 16-byte chunk), each
 // 64-channel line of a row copied by 16-byte DMA as in the forward kernel
-// (8 rows x 128 bytes per wave copy, chunks swizzled by chunk_swz of the
+// (8 rows x 128 bytes per wave copy, chunks swizzled by pixel_swz of the
 // pixel).  The instructions want 8 consecutive pixels per lane for one
 // channel; ds_read_b64_tr_b16 supplies them: in each group of 16 lanes, lane
 // (4i + q) points at channels 4q .. 4q + 3 of pixel row k0 + i, and lane j of
@@ -566,7 +577,7 @@ __device__ __forceinline__ short4v lds_read_tr16(const void* p)
 __device__ __forceinline__ int wtile_off(int k, int c, int NL)
 {
     return ((k >> 3) * NL + (c >> 6)) * 1024 + (k & 7) * 128 +
-           ((((c & 63) >> 3) ^ chunk_swz(k)) << 4) + (c & 7) * 2;
+           ((((c & 63) >> 3) ^ pixel_swz(k)) << 4) + (c & 7) * 2;
 }
 
 template <int WM, int WN, int MI, int NI, int NS>
@@ -598,15 +609,13 @@ conv_wgrad_bf16_kernel(const WgradBf16Params p)
     const int wn = wave / WM;
     const int n_rt = (p.Rw + TN - 1) / TN;
     const int n_mt = (p.Kg + TM - 1) / TM;
-    int T = blockIdx.x;
-    if (p.unit_order) {
-        // workgroups are dealt round-robin over the 8 XCDs: slot s of XCD x
-        // takes block s % U of unit (s / U) * 8 + x
-        const int U = n_rt * n_mt;
-        const int slot = blockIdx.x >> 3;
-        const int unit = (slot / U) * 8 + (blockIdx.x & 7);
-        T = unit * U + slot % U;
-    }
+    // XCD order: each XCD takes a contiguous run of tiles, so that the tiles of
+    // one (group, split) unit, which read the same slabs, share its L2.  The
+    // swizzle, this order and the split rule at N=512, kernels alone: conv1 201
+    // -> 185 us, conv2 313 -> 246, conv3 178 -> 154, conv4 187 -> 154, conv5 91
+    // -> 89 (before: whole units dealt to the XCDs from 7 tiles a unit on)
+    const int T = p.xcd_order ? (blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3)
+                              : (int)blockIdx.x;
     if (T >= n_rt * n_mt * p.G * p.splits)
         return;
     const int rt = T % n_rt;
@@ -623,7 +632,7 @@ conv_wgrad_bf16_kernel(const WgradBf16Params p)
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(p.X, p.X_bytes);
 
     // copies: this wave's row groups EA*wave + e (pixels 8*(EA*wave + e) +
-    // lane/8 of a stage), lane's chunk of a line (lane % 8) ^ chunk_swz(pixel).  Byte
+    // lane/8 of a stage), lane's chunk of a line (lane % 8) ^ pixel_swz(pixel).  Byte
     // offsets from a pixel: rows past Kg and columns past Rw are read (inside
     // the buffer or as zeros past its end) but feed only results that are
     // never stored, so they need no mask.
@@ -631,7 +640,7 @@ conv_wgrad_bf16_kernel(const WgradBf16Params p)
     uint32_t a_off[EA][NLA], b_off[EA][NLB];
 #pragma unroll
     for (int e = 0; e < EA; ++e) {
-        const int ch = (lane & 7) ^ chunk_swz(8 * (EA * wave + e) + cr);
+        const int ch = (lane & 7) ^ pixel_swz(cr);
 #pragma unroll
         for (int L = 0; L < NLA; ++L)
             a_off[e][L] = (uint32_t)(g * p.Kgp + m0 + 64 * L + 8 * ch) * 2u;
@@ -744,11 +753,32 @@ conv_wgrad_bf16_kernel(const WgradBf16Params p)
         }
     };
 
+    // Every kFlush turns of NS stages (1536 pixels) the accumulators move into
+    // a second set: short chains of additions, not one as long as the split
+    // (conv2 at N=512: error against 64 bits 4.3e-7 -> 2.7e-7, time the same).
+    constexpr int kFlush = 8;
+    floatx16 tot[MI][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+            tot[mi][ni] = floatx16{};
+    auto flush = [&]() {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                tot[mi][ni] += acc[mi][ni];
+                acc[mi][ni] = floatx16{};
+            }
+    };
+
     const int nst = col_end > col_begin ? (col_end - col_begin + TKP - 1) / TKP : 0;
     if (nst > 0)
         issue(0, A0, B0);
     if (NS > 2 && nst > 1)
         issue(1, A1, B1);
+    int left = kFlush;
     for (int s0 = 0; s0 < nst; s0 += NS) {
 #pragma unroll
         for (int h = 0; h < NS; ++h) {
@@ -774,7 +804,12 @@ conv_wgrad_bf16_kernel(const WgradBf16Params p)
                     issue_part(An, Bn, part);
             });
         }
+        if (--left == 0) {
+            flush();
+            left = kFlush;
+        }
     }
+    flush();
 
     // Partial result P[split][g*Kg + m][r], lanes along r
     const __amdgpu_buffer_rsrc_t rp = make_rsrc(p.P, p.P_bytes);
@@ -788,7 +823,7 @@ conv_wgrad_bf16_kernel(const WgradBf16Params p)
             for (int q = 0; q < 16; ++q) {
                 const int m = m0 + wm * MI * MT + mi * MT + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
                 const uint32_t bad = ((uint32_t)(m >= p.Kg) | (uint32_t)(r >= p.Rw)) << 31;
-                buf_st_f32(acc[mi][ni][q], rp,
+                buf_st_f32(tot[mi][ni][q], rp,
                            ((uint32_t)(pbase + (g * p.Kg + m) * p.Rw + r) * 4u) | bad);
             }
         }
@@ -1370,11 +1405,9 @@ template <int WM, int WN, int MI, int NI>
 hipError_t launch_wg(const WgradBf16Params& p, hipStream_t s)
 {
     constexpr int TM = WM * MI * 32, TN = WN * NI * 32;
-    const int64_t per_unit = (int64_t)((p.Rw + TN - 1) / TN) * ((p.Kg + TM - 1) / TM);
-    const int64_t units = (int64_t)p.G * p.splits;
-    // unit order: whole rounds of 8 units (the blocks past the last unit exit)
-    const int64_t tiles = p.unit_order ? (units + 7) / 8 * 8 * per_unit : units * per_unit;
-    if (tiles > INT_MAX)
+    const int64_t tiles = ((int64_t)((p.Rw + TN - 1) / TN) * ((p.Kg + TM - 1) / TM) * p.G *
+                               p.splits + 7) / 8 * 8;
+    if (tiles > INT_MAX / 2)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL((conv_wgrad_bf16_kernel<WM, WN, MI, NI, 3>), dim3((unsigned)tiles),
                        dim3(64 * WM * WN), 0, s, p);

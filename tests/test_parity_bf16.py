@@ -589,6 +589,24 @@ def test_wgrad_unit_order_bf16(case, overrides):
     assert_close(_np(dws[0]), dw_ref, TOL_F32, "weight gradient (rounded operands)")
 
 
+@pytest.mark.parametrize("K", [48, 128])  # the 96- and 128-row tiles
+@pytest.mark.parametrize("pixels", [1535, 1536, 1537, 1729, 3072, 3137])
+def test_wgrad_long_splits_bf16(pixels, K, overrides):
+    """One split of just below, at and above one and two turns of the second
+    accumulator set (24 stages of 64 pixels), against the oracle.  Products of
+    bf16 values are exact; each chain holds at most 1600 additions."""
+    print(f"bf16 wgrad long split pixels={pixels} K={K}", flush=True)
+    rng = np.random.default_rng([80, pixels, K])
+    xr = wl.round_bf16(rng.standard_normal((1, 16, 1, pixels)).astype(np.float32))
+    wr = wl.round_bf16(rng.standard_normal((K, 16, 1, 1)).astype(np.float32))
+    gd = wl.round_bf16(rng.standard_normal((1, K, 1, pixels)).astype(np.float32))
+    overrides.setenv("CAFFE_CONV_WGRAD_BLOCKS", "1")
+    _, dw, _ = cc.conv_backward(_t(xr, torch.bfloat16), _t(wr, torch.bfloat16), _t(gd), None, 1, 0,
+                                1, need=("dw",))
+    _, dw_ref, _ = oracle.conv_backward(xr, wr, gd, stride=1, pad=0, group=1, need=("dw",))
+    assert_close(_np(dw), dw_ref, 2.0 ** -24 * 1600, "weight gradient")
+
+
 @pytest.mark.parametrize("blocked", ["0", "1"])
 def test_dgrad_channel_blocked_bf16(blocked, overrides):
     """The data gradient with the reduction in 64-channel blocks outer, taps
