@@ -134,6 +134,7 @@ struct ConvPlan {
         size_t off_d, off_sums, off_wt, off_dpart, off_wpart, off_float, ws_back;
     } x3;
     bool dense;
+    int fc_few;  // forward: rows of W a block of the few-sample kernel, 0 for the GEMM
     int fc_tile_f, fc_tile_d, fc_tile_w;
     int fc_splits_f, fc_sps_f, fc_splits_d, fc_sps_d, fc_splits_w, fc_sps_w;
     size_t fc_off_xt, fc_off_wp, fc_off_pf;  // forward: [X^T][W^T] (C % 4 != 0)[partials]
@@ -927,6 +928,23 @@ int plan_conv(const caffe_conv_desc* d, ConvPlan* p)
         q.fc_tile_f = pick_dense_tile(std::max(N, 1), env_tile("CAFFE_FC_TILE_F"));
         q.fc_tile_d = pick_dense_tile(std::max(N, 1), env_tile("CAFFE_FC_TILE_D"));
         q.fc_tile_w = pick_dense_tile(K, env_tile("CAFFE_FC_TILE_W"));
+        // Few samples: the kernel that streams W once (the tile and split
+        // settings are the GEMM's).  us, GEMM and reduce -> this, on K x C:
+        // 4096 x 9216 N=1 47.8 -> 27.6, N=8 48.7 -> 43.4; 4096 x 4096 23.7 ->
+        // 11.4 and 24.2 -> 21.3; 500 x 800 7.1 -> 2.6 and 7.4 -> 4.4; 777 x 5001
+        // 26.6 -> 5.5 and 27.0 -> 11.4.  On rows of 300 the blocks are short
+        // and the GEMM is as fast from 6 samples on (8.0 against 9.1 at 8).
+        // Several rows a block save reads of X, which pays on large W and
+        // from a few samples on (4096 x 9216, N=8: 69 us with 1 row, 52 with 2;
+        // 4096 x 4096 25, 21 and 22 with 4; 1000 x 4096 9, 10 and 13).
+        q.fc_few = 0;
+        const int few = env_tile("CAFFE_FC_FEW");
+        if (N <= kDenseFewMax && (N <= 5 || C >= 512 || few > 0) &&
+            env_tile("CAFFE_FC_TILE_F") < 0 && env_tile("CAFFE_FC_SPLITS_F") < 0 && few != 0)
+            q.fc_few = few > 0                                         ? few
+                       : N > 1 && (int64_t)K * C >= (int64_t(1) << 25) ? 4
+                       : N > 2 && (int64_t)K * C >= (int64_t(1) << 23) ? 2
+                                                                       : 1;
         plan_splits(N, K, C, q.fc_tile_f, device_cu_count(),
                     env_tile("CAFFE_FC_SPLITS_F"), &q.fc_splits_f, &q.fc_sps_f);
         plan_splits(N, C, K, q.fc_tile_d, device_cu_count(),
@@ -1426,6 +1444,11 @@ int run_dense_forward(const ConvPlan& q, const float* bottom, const float* weigh
     const int N = q.N, C = q.C, K = q.K;
     if (N == 0)
         return CAFFE_OK;
+    if (q.fc_few) {
+        LAUNCH(launch_dense_few_forward(bottom, weight, bias, N, C, K, q.relu, top, q.fc_few, s),
+               "inner-product forward launch");
+        return CAFFE_OK;
+    }
     float* part = (float*)(ws + q.fc_off_pf);
     if (C % 4 == 0) {
         // both operands as stored: X [N][C] and W [K][C], C contiguous (and

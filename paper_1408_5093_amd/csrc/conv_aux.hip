@@ -257,17 +257,205 @@ hipError_t launch_transpose_f32(const float* in, float* out, int R, int C, hipSt
     return hipGetLastError();
 }
 
-// Split-K partials added in order (s = 0, 1, ...), then the bias and ReLU.
+// Inner product of few samples, Y[n][k] = relu(b[k] + sum_c X[n][c] W[k][c]):
+// bound by W, which a block of 256 threads streams once, RB rows at a time,
+// against NB = N rows of X from the L2.  A thread adds every 256th float (or
+// 16 bytes, VEC: C a multiple of 4), butterflies across the wave and the four
+// waves' sums in order follow: chains of C / 256 terms and no partials in
+// memory.  One image, MI355X, GEMM and split reduce before -> now: 4096 x 9216
+// 47.8 us -> 27.6 (5.5 TB/s of W), 4096 x 4096 23.7 -> 11.4, 1000 x 4096 12.6 ->
+// 4.8.
+template <int NB, int RB, bool VEC>
+__global__ void __launch_bounds__(256)
+dense_few_forward_kernel(const float* __restrict__ X, const float* __restrict__ W,
+                         const float* __restrict__ bias, int C, int K, int relu,
+                         float* __restrict__ Y)
+{
+    constexpr int V = VEC ? 4 : 1;
+    constexpr int U = RB >= 4 ? 2 : 4;  // chunks of a row under way
+    typedef float vec __attribute__((ext_vector_type(V)));
+    __shared__ float sums[4][RB * NB];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k0 = blockIdx.x * RB;
+    const float* w[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+        w[r] = W + (size_t)min(k0 + r, K - 1) * C;  // (a row past K is read, not stored)
+    float acc[RB][NB] = {};
+    auto chunk = [&](const vec (&wv)[RB], int c) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            const vec xv = *(const vec*)(X + (size_t)n * C + c);
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    acc[r][n] = fmaf(wv[r][v], xv[v], acc[r][n]);
+        }
+    };
+    int c = V * tid;
+    for (; c + (U - 1) * 256 * V < C; c += U * 256 * V) {
+        vec wv[U][RB];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+                wv[u][r] = *(const vec*)(w[r] + c + u * 256 * V);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            chunk(wv[u], c + u * 256 * V);
+    }
+    for (; c < C; c += 256 * V) {
+        vec wv[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+            wv[r] = *(const vec*)(w[r] + c);
+        chunk(wv, c);
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            float t = acc[r][n];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+                t += __shfl_xor(t, o, 64);
+            if (lane == 0)
+                sums[wave][r * NB + n] = t;
+        }
+    __syncthreads();
+    for (int i = tid; i < RB * NB; i += 256) {
+        const int k = k0 + i / NB, n = i % NB;
+        if (k >= K)
+            continue;
+        float t = ((sums[0][i] + sums[1][i]) + sums[2][i]) + sums[3][i];
+        if (bias)
+            t += bias[k];
+        if (relu && !(t > 0.f))
+            t = 0.f;
+        Y[(size_t)n * K + k] = t;
+    }
+}
+
+namespace {
+template <int NB>
+hipError_t launch_few(const float* X, const float* W, const float* bias, int C, int K, int relu,
+                      float* Y, int rows, hipStream_t s)
+{
+    auto go = [&](auto kernel, int rb) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((K + rb - 1) / rb)), dim3(256), 0, s, X, W,
+                           bias, C, K, relu, Y);
+        return hipGetLastError();
+    };
+    if (C % 4 == 0)
+        return rows == 4   ? go(dense_few_forward_kernel<NB, 4, true>, 4)
+               : rows == 2 ? go(dense_few_forward_kernel<NB, 2, true>, 2)
+                           : go(dense_few_forward_kernel<NB, 1, true>, 1);
+    return rows == 4   ? go(dense_few_forward_kernel<NB, 4, false>, 4)
+           : rows == 2 ? go(dense_few_forward_kernel<NB, 2, false>, 2)
+                       : go(dense_few_forward_kernel<NB, 1, false>, 1);
+}
+}  // namespace
+
+hipError_t launch_dense_few_forward(const float* X, const float* W, const float* bias, int N,
+                                    int C, int K, int relu, float* Y, int rows, hipStream_t s)
+{
+    if (N == 0 || K == 0)
+        return hipSuccess;
+    if (C % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) != 0)
+        return hipErrorInvalidValue;
+    switch (N) {
+    case 1:
+        return launch_few<1>(X, W, bias, C, K, relu, Y, rows, s);
+    case 2:
+        return launch_few<2>(X, W, bias, C, K, relu, Y, rows, s);
+    case 3:
+        return launch_few<3>(X, W, bias, C, K, relu, Y, rows, s);
+    case 4:
+        return launch_few<4>(X, W, bias, C, K, relu, Y, rows, s);
+    case 5:
+        return launch_few<5>(X, W, bias, C, K, relu, Y, rows, s);
+    case 6:
+        return launch_few<6>(X, W, bias, C, K, relu, Y, rows, s);
+    case 7:
+        return launch_few<7>(X, W, bias, C, K, relu, Y, rows, s);
+    case 8:
+        return launch_few<8>(X, W, bias, C, K, relu, Y, rows, s);
+    default:
+        return hipErrorInvalidValue;
+    }
+}
+
+// Split-K partials of one output, P[q * stride], q = 0 .. splits - 1.  With
+// one part a thread adds them all in order; with PARTS the lanes of a block
+// stand as PARTS groups of 256 / PARTS columns, group g adds terms g, g + PARTS,
+// ... and its first group the PARTS sums in order: more loads in flight
+// where the outputs are few and the splits many.  Four loads are under way at
+// a time in either form.
+template <int PARTS>
+__device__ __forceinline__ float sum_splits(const float* P, int splits, int64_t stride, int part,
+                                            float t)
+{
+    int q = part;
+    for (; q + 3 * PARTS < splits; q += 4 * PARTS) {
+        const float a0 = P[q * stride];
+        const float a1 = P[(q + PARTS) * stride];
+        const float a2 = P[(q + 2 * PARTS) * stride];
+        const float a3 = P[(q + 3 * PARTS) * stride];
+        t += a0;
+        t += a1;
+        t += a2;
+        t += a3;
+    }
+    for (; q < splits; q += PARTS)
+        t += P[q * stride];
+    return t;
+}
+
+// The parts' sums of a block's columns added up (every thread calls).
+template <int PARTS>
+__device__ __forceinline__ float sum_parts(float t, int part, int col)
+{
+    if constexpr (PARTS == 1) {
+        return t;
+    } else {
+        __shared__ float sums[PARTS][256 / PARTS + 1];
+        sums[part][col] = t;
+        __syncthreads();
+        t = 0.f;
+        if (part == 0) {
+#pragma unroll
+            for (int i = 0; i < PARTS; ++i)
+                t += sums[i][col];
+        }
+        __syncthreads();
+        return t;
+    }
+}
+
+// Parts for `count` outputs: eight where one thread per output would give
+// the device less than four waves a SIMD unit and each has eight terms or more
+// (one image through CaffeNet, MI355X, the five forward reduces: 39.9 us -> 23.8).
+static bool split_in_parts(int64_t count, int splits)
+{
+    return count <= 1024 * 256 && splits >= 8;
+}
+
+// Split-K partials, then the bias and ReLU.
+template <int PARTS>
 __global__ void __launch_bounds__(256)
 split_reduce_kernel(const float* __restrict__ P, int splits, int count, int ncol,
                     const float* __restrict__ bias, int relu, const float* __restrict__ mask,
                     float* __restrict__ out)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += gridDim.x * blockDim.x) {
-        float t = 0.f;
-        for (int q = 0; q < splits; ++q)
-            t += P[(size_t)q * count + i];
+    constexpr int COLS = 256 / PARTS;
+    const int col = threadIdx.x % COLS, part = threadIdx.x / COLS;
+    for (int i0 = blockIdx.x * COLS; i0 < count; i0 += gridDim.x * COLS) {
+        const int i = i0 + col;
+        float t = i < count ? sum_splits<PARTS>(P + i, splits, count, part, 0.f) : 0.f;
+        t = sum_parts<PARTS>(t, part, col);
+        if (part != 0 || i >= count)
+            continue;
         if (bias)
             t += bias[i % ncol];
         if (relu && !(t > 0.f))
@@ -283,11 +471,12 @@ hipError_t launch_split_reduce(const float* P, int splits, int count, int ncol, 
 {
     if (count == 0)
         return hipSuccess;
-    int blocks = (count + 255) / 256;
+    const bool parts = split_in_parts(count, splits);
+    int blocks = (int)(((int64_t)count + (parts ? 31 : 255)) / (parts ? 32 : 256));
     if (blocks > 8192)
         blocks = 8192;
-    hipLaunchKernelGGL(split_reduce_kernel, dim3(blocks), dim3(256), 0, s, P, splits, count, ncol,
-                       bias, relu, mask, out);
+    hipLaunchKernelGGL(parts ? split_reduce_kernel<8> : split_reduce_kernel<1>, dim3(blocks),
+                       dim3(256), 0, s, P, splits, count, ncol, bias, relu, mask, out);
     return hipGetLastError();
 }
 
@@ -295,37 +484,52 @@ hipError_t launch_split_reduce(const float* P, int splits, int count, int ncol, 
 // col fastest (coalesced partial reads); the partials of an output are added
 // in split order after the bias.
 // The region: groups g0 .. g0 + Gt - 1, columns c0 .. c0 + Nc - 1.
+template <int PARTS>
 __global__ void __launch_bounds__(256)
 conv_split_reduce_fwd_kernel(const float* __restrict__ P, int splits, int g0, int Gt, int M,
                              int c0, int Nc, int OHW, int Cout, const float* __restrict__ bias,
                              int relu, float* __restrict__ Y)
 {
-    const int64_t count = (int64_t)Gt * M * Nc;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int col = c0 + (int)(e % Nc);
-        const int gm = g0 * M + (int)(e / Nc);     // g * M + m = output channel
-        float t = bias ? bias[gm] : 0.f;
-        for (int q = 0; q < splits; ++q)
-            t += P[(int64_t)q * count + e];
+    const uint32_t count = (uint32_t)Gt * M * Nc;  // (< 2^29, see the launchers)
+    constexpr int COLS = 256 / PARTS;
+    const uint32_t lcol = threadIdx.x % COLS, part = threadIdx.x / COLS;
+    for (uint32_t e0 = blockIdx.x * COLS; e0 < count; e0 += gridDim.x * COLS) {
+        const uint32_t e = e0 + lcol;
+        const uint32_t mc = e / (uint32_t)Nc;
+        const int gm = g0 * M + (int)mc;  // g * M + m = output channel
+        float t = bias && part == 0 && e < count ? bias[gm] : 0.f;
+        if (e < count)
+            t = sum_splits<PARTS>(P + e, splits, count, part, t);
+        t = sum_parts<PARTS>(t, part, lcol);
+        if (part != 0 || e >= count)
+            continue;
+        const int col = c0 + (int)(e - mc * Nc);
         const int n = col / OHW;
         const int pix = col - n * OHW;
         Y[((int64_t)n * Cout + gm) * OHW + pix] = t > 0.f ? t : (relu ? 0.f : t);
     }
 }
 
+template <int PARTS>
 __global__ void __launch_bounds__(256)
 conv_split_reduce_dgrad_kernel(const float* __restrict__ P, int splits, int g0, int Gt, int M,
                                int c0, int Nc, int OHW, int OW, int psh, int psw, int a0h,
                                int a0w, int oph, int opw, int Cout, int Cg_out, int OutH,
                                int OutW, const float* __restrict__ mask, float* __restrict__ dX)
 {
-    const int64_t count = (int64_t)Gt * M * Nc;
+    const uint32_t count = (uint32_t)Gt * M * Nc;  // (< 2^29, see the launchers)
     const int pss = psh * psw;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int col = c0 + (int)(e % Nc);
-        const int gm = g0 * M + (int)(e / Nc);
+    constexpr int COLS = 256 / PARTS;
+    const uint32_t lcol = threadIdx.x % COLS, part = threadIdx.x / COLS;
+    for (uint32_t e0 = blockIdx.x * COLS; e0 < count; e0 += gridDim.x * COLS) {
+        const uint32_t e = e0 + lcol;
+        float t = e < count ? sum_splits<PARTS>(P + e, splits, count, part, 0.f) : 0.f;
+        t = sum_parts<PARTS>(t, part, lcol);
+        if (part != 0 || e >= count)
+            continue;
+        const uint32_t mc = e / (uint32_t)Nc;
+        const int col = c0 + (int)(e - mc * Nc);
+        const int gm = g0 * M + (int)mc;
         const int g = gm / M;
         const int m = gm - g * M;
         const int c = m / pss;
@@ -340,9 +544,6 @@ conv_split_reduce_dgrad_kernel(const float* __restrict__ P, int splits, int g0, 
         const int w = psw * (b + a0w) - opw + fw;
         if ((unsigned)h >= (unsigned)OutH || (unsigned)w >= (unsigned)OutW)
             continue;
-        float t = 0.f;
-        for (int q = 0; q < splits; ++q)
-            t += P[(int64_t)q * count + e];
         const int64_t o = (((int64_t)n * Cout + g * Cg_out + c) * OutH + h) * OutW + w;
         if (mask && !(mask[o] > 0.f))
             t = 0.f;
@@ -359,10 +560,14 @@ hipError_t launch_conv_split_reduce_fwd(const float* P, int splits, const ConvGe
     const int64_t count = (int64_t)Gt * q.M * Nc;
     if (count == 0)
         return hipSuccess;
-    int64_t blocks = (count + 255) / 256;
+    if (count >= (int64_t(1) << 29))  // the partials stay below 2^31 bytes
+        return hipErrorInvalidValue;
+    const bool parts = split_in_parts(count, splits);
+    int64_t blocks = (count + (parts ? 31 : 255)) / (parts ? 32 : 256);
     if (blocks > 8192)
         blocks = 8192;
-    hipLaunchKernelGGL(conv_split_reduce_fwd_kernel, dim3((unsigned)blocks), dim3(256), 0, s, P,
+    hipLaunchKernelGGL(parts ? conv_split_reduce_fwd_kernel<8> : conv_split_reduce_fwd_kernel<1>,
+                       dim3((unsigned)blocks), dim3(256), 0, s, P,
                        splits, g0, Gt, q.M, c0, Nc, q.OH * q.OW, q.Cout, q.bias, q.relu, Y);
     return hipGetLastError();
 }
@@ -377,10 +582,14 @@ hipError_t launch_conv_split_reduce_dgrad(const float* P, int splits, const Conv
     const int64_t count = (int64_t)Gt * q.M * Nc;
     if (count == 0)
         return hipSuccess;
-    int64_t blocks = (count + 255) / 256;
+    if (count >= (int64_t(1) << 29))  // the partials stay below 2^31 bytes
+        return hipErrorInvalidValue;
+    const bool parts = split_in_parts(count, splits);
+    int64_t blocks = (count + (parts ? 31 : 255)) / (parts ? 32 : 256);
     if (blocks > 8192)
         blocks = 8192;
-    hipLaunchKernelGGL(conv_split_reduce_dgrad_kernel, dim3((unsigned)blocks), dim3(256), 0, s, P,
+    hipLaunchKernelGGL(parts ? conv_split_reduce_dgrad_kernel<8> : conv_split_reduce_dgrad_kernel<1>,
+                       dim3((unsigned)blocks), dim3(256), 0, s, P,
                        splits, g0, Gt, q.M, c0, Nc, q.OH * q.OW, q.OW, q.psh, q.psw, q.a0h,
                        q.a0w, q.oph, q.opw, q.Cout, q.Cg_out, q.OutH, q.OutW, mask, dX);
     return hipGetLastError();

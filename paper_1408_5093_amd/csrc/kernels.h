@@ -87,6 +87,12 @@ int device_cu_count();
 // out[c][r] = in[r][c] for an R x C row-major float matrix.
 hipError_t launch_transpose_f32(const float* in, float* out, int R, int C, hipStream_t s);
 
+// Inner product of N <= kDenseFewMax samples, `rows` (1, 2 or 4) rows of W a
+// block: Y[n][k] = relu(bias[k] + sum_c X[n][c] W[k][c]).
+constexpr int kDenseFewMax = 8;
+hipError_t launch_dense_few_forward(const float* X, const float* W, const float* bias, int N,
+                                    int C, int K, int relu, float* Y, int rows, hipStream_t s);
+
 // D = G [Y > 0] element by element.
 hipError_t launch_relu_mask(const float* G, const float* Y, float* D, int64_t count, hipStream_t s);
 // out[i] = act(sum_{s < splits} P[s*count + i] + bias[i % ncol]) in a fixed

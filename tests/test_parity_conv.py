@@ -229,6 +229,16 @@ def test_split_k(case, splits, blocked, overrides):
 
 
 @pytest.mark.parametrize("case", SPLIT_CASES)
+@pytest.mark.parametrize("splits", [8, 11])
+def test_split_k_in_parts(case, splits, overrides):
+    """Eight splits and more: the reduces add them in eight parts, whole and
+    ragged."""
+    overrides.setenv("CAFFE_CONV_FWD_SPLITS", str(splits))
+    overrides.setenv("CAFFE_CONV_DGRAD_SPLITS", str(splits))
+    run_case(*case, relu=True, bias=True)
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES)
 @pytest.mark.parametrize("splits,units", [(2, 1), (3, 2)])
 def test_tail_split(case, splits, units, overrides):
     """Tail splits (the last column tiles of the last group cut into

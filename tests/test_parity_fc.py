@@ -183,3 +183,53 @@ def test_caffenet_fc_full_size(l):
     check_layer_sampled(L, inp["x"], inp["W"], inp["b"], _np(y), inp["top_diff"], _np(dx),
                         _np(dw), _np(db), images=[0, 129, N - 1], filters=[0, L.K // 2, L.K - 1],
                         what=L.name)
+
+
+def _few_bound(x, w, b, C):
+    # chains of C / 256 fused additions a thread, then the wave's butterfly,
+    # four waves and the bias: (C / 256 + 12) half-ulps of the sum of magnitudes
+    mag = np.abs(x.reshape(len(x), -1).astype(np.float64)) @ np.abs(
+        w.reshape(len(w), -1).T.astype(np.float64)) + np.abs(b)
+    return (C / 256 + 12) * 2.0 ** -24 * mag
+
+
+@pytest.mark.parametrize("rows", [1, 2, 4])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_few_samples(N, rows, overrides):
+    """The few-sample forward kernel at ragged and whole row blocks, with C a
+    multiple of 4 or not, below, at and past its 256-thread chunks."""
+    overrides.setenv("CAFFE_FC_FEW", str(rows))
+    for C, K in ((1, 1), (3, 5), (4, 7), (255, 3), (256, 9), (1023, 6), (1024, 4), (1028, 13),
+                 (2051, 2), (4100, 5), (9216, 33)):
+        print(f"few samples N={N} C={C} K={K} rows={rows}", flush=True)
+        rng = np.random.default_rng([81, N, C, K])
+        x = rng.standard_normal((N, C, 1, 1)).astype(np.float32)
+        w = (rng.standard_normal((K, C, 1, 1)) / np.sqrt(C)).astype(np.float32)
+        b = rng.standard_normal(K).astype(np.float32)
+        for relu in (False, True):
+            y = _np(cc.conv_forward(_t(x), _t(w), _t(b), 1, 0, 1, relu)).reshape(N, K)
+            ref = (x.reshape(N, C).astype(np.float64) @ w.reshape(K, C).T.astype(np.float64)) + b
+            ref = np.maximum(ref, 0) if relu else ref
+            assert (np.abs(y - ref) <= _few_bound(x, w, b, C)).all()
+
+
+@pytest.mark.parametrize("case", [(3, 160, 70), (8, 16 * 33, 130), (2, 2048, 64)])
+@pytest.mark.parametrize("splits", [7, 8, 9, 33])
+def test_few_samples_gemm_splits(case, splits, overrides):
+    """The GEMM path on few samples, its partials added in one part (below 8
+    splits) and in eight, ragged and whole."""
+    overrides.setenv("CAFFE_FC_FEW", "0")
+    overrides.setenv("CAFFE_FC_SPLITS_F", str(splits))
+    overrides.setenv("CAFFE_FC_SPLITS_D", str(splits))
+    run_fc(*case, True, seed=1)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_few_samples_special_values(value):
+    """Infinities and NaN in one weight reach their output and no other."""
+    x = np.ones((2, 300, 1, 1), np.float32)
+    w = np.ones((6, 300, 1, 1), np.float32)
+    w[4, 299] = value
+    y = _np(cc.conv_forward(_t(x), _t(w), None, 1, 0, 1, False)).reshape(2, 6)
+    assert (y[:, [0, 1, 2, 3, 5]] == 300).all()
+    np.testing.assert_array_equal(y[:, 4], np.full(2, value, np.float32))
