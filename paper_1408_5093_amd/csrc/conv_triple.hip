@@ -93,9 +93,9 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t t[3])
 }
 
 // Eight floats -> one unit (three 16-byte chunks at dst).
-__device__ __forceinline__ void store_unit(const float v[8], bf16_t* dst)
+// The three terms of eight floats, a 16-byte chunk each.
+__device__ __forceinline__ void unit_terms(const float v[8], u32x4 o[3])
 {
-    u32x4 o[3];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         uint32_t t[3];
@@ -104,9 +104,45 @@ __device__ __forceinline__ void store_unit(const float v[8], bf16_t* dst)
         for (int p = 0; p < 3; ++p)
             o[p][k] = t[p];
     }
+}
+
+__device__ __forceinline__ void store_unit(const float v[8], bf16_t* dst)
+{
+    u32x4 o[3];
+    unit_terms(v, o);
 #pragma unroll
     for (int p = 0; p < 3; ++p)
         ((u32x4*)dst)[p] = o[p];
+}
+
+// The twelve chunks of four neighbouring lanes' units (lane u = lane % 4 holds
+// unit u, all four active) in place: lane u stores chunks u, 4 + u, 8 + u of the
+// 192 bytes at dst, so that a store's lanes are contiguous; chunk j, term j % 3
+// of unit j / 3, comes across the quad.  Units from `units` on aren't stored.
+__device__ __forceinline__ void store_quad(const u32x4 o[3], int u, int units, bf16_t* dst)
+{
+    constexpr int kPerm[3] = {0x40, 0xA5, 0xFE};  // lane (4 s + u) / 3 for lane u
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const int j = 4 * s + u;
+        const int unit = (j * 11) >> 5;  // j / 3
+        const int term = j - 3 * unit;
+        u32x4 c;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            uint32_t t[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const int x = (int)o[p][k];
+                t[p] = s == 0   ? __builtin_amdgcn_mov_dpp(x, kPerm[0], 0xf, 0xf, true)
+                       : s == 1 ? __builtin_amdgcn_mov_dpp(x, kPerm[1], 0xf, 0xf, true)
+                                : __builtin_amdgcn_mov_dpp(x, kPerm[2], 0xf, 0xf, true);
+            }
+            c[k] = term == 0 ? t[0] : term == 1 ? t[1] : t[2];
+        }
+        if (unit < units)
+            ((u32x4*)dst)[j] = c;
+    }
 }
 
 template <int MT>
@@ -899,7 +935,10 @@ conv_wgrad_x3_kernel(const WgradX3Params p)
 // bordered rows r0 .. r0 + RH - 1: the real rows among them are one contiguous
 // run of at most 256 pixels per channel plane, one pixel per thread with all
 // 32 channels' loads in flight; the floats cross LDS and each thread writes
-// whole units.  Streams: bound by HBM.  sums (may be null): the block's sum of
+// whole units, the four units of a pixel across a quad.  Streams: bound by HBM.
+// (Blocks linear and three 16-byte stores 48 bytes apart a lane -> this, 256
+// images: 96 x 27 x 27 for conv2 69 us -> 54, its masked top gradient 182 -> 158;
+// the eight of a training step 570 -> 446.)  sums (may be null): the block's sum of
 // each channel's (masked) floats, sums[(g*Kg + c) * T + n * rchunks + chunk]
 // (T = N * rchunks), for the bias gradient.
 constexpr int kX3Ch = 32;
@@ -912,8 +951,13 @@ stage_x3_kernel(const float* __restrict__ X, const float* __restrict__ Y, bf16_t
                 int Hp, int Wp, int tb, int lb, int RH, int rchunks, int ctiles)
 {
     __shared__ float tile[kX3Ch][kX3Pix + 2];
-    const int n = blockIdx.x / (rchunks * ctiles);
-    const int rem = blockIdx.x - n * rchunks * ctiles;
+    // each XCD takes a contiguous run of blocks: the channel tiles of a pixel,
+    // whose 192-byte runs share lines, meet in one L2
+    const int b = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int n = b / (rchunks * ctiles);
+    if (n >= N)
+        return;
+    const int rem = b - n * rchunks * ctiles;
     const int rc = rem / ctiles;
     const int c0 = (rem - rc * ctiles) * kX3Ch;
     const int r0 = rc * RH;
@@ -970,30 +1014,27 @@ stage_x3_kernel(const float* __restrict__ X, const float* __restrict__ Y, bf16_t
     }
     const int npix = (r1 - r0) * Wp;
     constexpr int U = kX3Ch / 8;
+    static_assert(U == 4, "a quad stores a pixel's units");
     for (int id = tid; id < npix * U; id += 256) {
+        // (a quad's four units are of one pixel: its lanes run alike)
         const int u = id % U;
         const int pl = id / U;
-        const int cp = c0 + 8 * u;
-        if (cp >= Ctot)
-            continue;
         const int pr = pl / Wp;
         const int hp = r0 + pr;
         const int wp = pl - pr * Wp;
         const int h = hp - tb;
         const int w = wp - lb;
-        bf16_t* dst = &Xp[((((size_t)n * Hp + hp) * Wp + wp) * Ctot + cp) * 3];
+        u32x4 o[3] = {};
         if ((unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W) {
             const int q = (h - h0) * W + w;
             float v[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 v[k] = tile[8 * u + k][q];
-            store_unit(v, dst);
-        } else {
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                ((u32x4*)dst)[p] = u32x4{0u, 0u, 0u, 0u};
+            unit_terms(v, o);
         }
+        store_quad(o, u, (Ctot - c0) / 8,
+                   &Xp[((((size_t)n * Hp + hp) * Wp + wp) * Ctot + c0) * 3]);
     }
 }
 
@@ -1014,7 +1055,7 @@ hipError_t launch_stage_x3(const float* X, const float* Y, uint16_t* Xp, float* 
     const int RH = kX3Pix / W;
     const int rchunks = stage_x3_chunks(W, Hp);
     const int ctiles = (Ctot + kX3Ch - 1) / kX3Ch;
-    const dim3 grid((unsigned)((int64_t)N * rchunks * ctiles));
+    const dim3 grid((unsigned)(((int64_t)N * rchunks * ctiles + 7) / 8 * 8));
     if (Y)
         hipLaunchKernelGGL(stage_x3_kernel<true>, grid, dim3(256), 0, s, X, Y, Xp, sums, N, C, H,
                            W, Cg, Cgp, Ctot, Hp, Wp, tb, lb, RH, rchunks, ctiles);
