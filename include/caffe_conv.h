@@ -70,7 +70,8 @@
  * thread.
  *
  * Tuning.  Tile shapes, split counts and kernel variants are chosen from the
- * descriptor alone.  Environment variables named CAFFE_CONV_*, CAFFE_FC_*,
+ * descriptor, and between float and three-term operands also by the workspace
+ * given (caffe_conv_workspace_preferred).  Environment variables named CAFFE_CONV_*, CAFFE_FC_*,
  * CAFFE_BF16_* and CAFFE_BACKWARD_FORK override those choices for profiling
  * and tests, and are read only while CAFFE_PROFILE_OVERRIDES=1 is set.
  */
