@@ -46,13 +46,14 @@ constexpr int kRowC = 12;    // 16-byte chunks per operand row and stage
 // Slot of unit j within its term's four chunks of LDS row r: j ^ row_swz(r).
 __device__ __forceinline__ int row_swz(int r) { return (-(r >> 2)) & 3; }
 
-// The three bf16 terms of a pair of floats, packed (x low, y high).  The
-// terms of a value that is no ordinary float keep its products what they are
-// in float arithmetic (the products taken are 00, 01, 10, 11, 02 and 20):
-//  NaN: (NaN, 0, 0); +-inf: (+-1, 0, +-inf), so that against a finite y the
-//  infinity meets only y0 (zero exactly when y is), and against another
-//  infinity the 1 there; a finite value that rounds to infinity (at least
-//  2^128 - 2^119) takes the largest bf16 below it as its first term.
+// A float that its first term can't stand for -- infinity, NaN, a finite value
+// that rounds to bf16's infinity -- is staged as this NaN and its own upper and
+// lower 16 bits.  The NaN reaches every output that the value enters, and such
+// outputs are formed again in float arithmetic (x3_float, the end of both
+// kernels).
+constexpr uint32_t kMark = 0x7fc0;
+
+// The three bf16 terms of a pair of floats, packed (x low, y high).
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t t[3])
 {
     t[0] = f32x2_to_bf16x2_rne(x, y);
@@ -61,35 +62,29 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t t[3])
     t[1] = f32x2_to_bf16x2_rne(rx, ry);
     t[2] = f32x2_to_bf16x2_rne(rx - __builtin_bit_cast(float, t[1] << 16),
                                ry - __builtin_bit_cast(float, t[1] & 0xffff0000u));
-    const uint32_t ax = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
-    const uint32_t ay = __builtin_bit_cast(uint32_t, y) & 0x7fffffffu;
+    const uint32_t ux = __builtin_bit_cast(uint32_t, x), uy = __builtin_bit_cast(uint32_t, y);
+    const uint32_t ax = ux & 0x7fffffffu, ay = uy & 0x7fffffffu;
     if (__builtin_expect((ax > ay ? ax : ay) >= 0x7f7f8000u, 0)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const float v = h ? y : x;
-            const uint32_t u = __builtin_bit_cast(uint32_t, v), a = u & 0x7fffffffu;
-            if (a < 0x7f7f8000u)
+            const uint32_t u = h ? uy : ux;
+            if ((h ? ay : ax) < 0x7f7f8000u)
                 continue;
-            uint32_t w0, w1 = 0, w2 = 0;
-            const uint32_t sg = (u >> 16) & 0x8000u;
-            if (a > 0x7f800000u) {
-                w0 = (u >> 16) | 0x40u;
-            } else if (a == 0x7f800000u) {
-                w0 = sg | 0x3f80u;
-                w2 = sg | 0x7f80u;
-            } else {
-                w0 = u >> 16;
-                const float r = v - __builtin_bit_cast(float, u & 0xffff0000u);
-                w1 = f32_to_bf16_rne(r);
-                w2 = f32_to_bf16_rne(r - bf16_to_f32((uint16_t)w1));
-            }
             const uint32_t keep = h ? 0x0000ffffu : 0xffff0000u;
             const int sh = 16 * h;
-            t[0] = (t[0] & keep) | (w0 << sh);
-            t[1] = (t[1] & keep) | (w1 << sh);
-            t[2] = (t[2] & keep) | (w2 << sh);
+            t[0] = (t[0] & keep) | (kMark << sh);
+            t[1] = (t[1] & keep) | ((u >> 16) << sh);
+            t[2] = (t[2] & keep) | ((u & 0xffffu) << sh);
         }
     }
+}
+
+// The float that three terms (16 bits each) stand for.
+__device__ __forceinline__ float x3_float(uint32_t t0, uint32_t t1, uint32_t t2)
+{
+    const float sum = (__builtin_bit_cast(float, t0 << 16) + __builtin_bit_cast(float, t1 << 16)) +
+                      __builtin_bit_cast(float, t2 << 16);
+    return t0 == kMark ? __builtin_bit_cast(float, (t1 << 16) | t2) : sum;
 }
 
 // Eight floats -> one unit (three 16-byte chunks at dst).
@@ -534,11 +529,29 @@ conv_gemm_x3_kernel(const GemmX3Params p)
         mul(0, 0, 2);
         mul(0, 2, 0);
     }
+    float odd = 0.f;  // (NaN once a sum is infinite or NaN)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < NI; ++ni) {
             acc[mi][ni] += lo[mi][ni];
+#pragma unroll
+            for (int q = 0; q < Op::kRegs; ++q)
+                odd = fmaf(acc[mi][ni][q], 0.f, odd);
+        }
+    // the lane's outputs to form again, a bit each
+    static_assert(MI * NI * Op::kRegs <= 64, "one bit per output");
+    uint64_t again = 0;
+    if (__builtin_expect(odd != odd, 0)) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int q = 0; q < Op::kRegs; ++q)
+                    again |= (uint64_t)!__builtin_isfinite(acc[mi][ni][q])
+                             << ((mi * NI + ni) * Op::kRegs + q);
+    }
 
     // ---- epilogue (branch-free: masked lanes store to an out-of-range offset)
     const __amdgpu_buffer_rsrc_t ry = make_rsrc(p.Y, p.Y_bytes);
@@ -568,9 +581,7 @@ conv_gemm_x3_kernel(const GemmX3Params p)
                     buf_st_f32(acc[mi][ni][q], rp, off);
                 }
             }
-        return;
-    }
-    if constexpr (EPI == 0) {
+    } else if constexpr (EPI == 0) {
         int cbase[NI];
         uint32_t cbad[NI];
 #pragma unroll
@@ -655,6 +666,93 @@ conv_gemm_x3_kernel(const GemmX3Params p)
                     }
             }
     }
+
+    // ---- sums that came out infinite or NaN, formed again in float
+    // arithmetic and stored over: an operand is no ordinary float, or a product
+    // overflows (the small products, of any sign, then overflow as well and
+    // would make NaN of infinity).  A lane forms its outputs one after the
+    // other, each until it is NaN: a path for blobs that are diverging (conv2's
+    // forward at N = 64: 0.28 ms, with one infinity 3.5, all infinite 10, all
+    // NaN 2.2; backward 0.5, 12, 30 and 1.1).
+    if (__builtin_expect(again == 0, 1))
+        return;
+    __builtin_amdgcn_s_waitcnt(kVmcnt0);
+    const int first_s = ORD == 2 ? p.ntap / 2 : (nst - s_begin) / 2;
+    do {
+        const int bit = __builtin_ctzll(again);
+        again &= again - 1;
+        const int blk = bit / Op::kRegs;
+        const int m = m0 + wm * MI * MT + blk / NI * MT + Op::row(bit % Op::kRegs, le);
+        const int col = n0 + brow + blk % NI * MT;
+        if (m >= M || col >= p.Ncol)
+            continue;
+        const int n = (int)fdiv((uint32_t)col, p.div_ohw);
+        const int pix = col - n * OHW;
+        const int i = (int)fdiv((uint32_t)pix, p.div_ow);
+        const int j = pix - i * p.OW;
+        const uint32_t at = (uint32_t)(((n * p.IHp + i * p.sh + p.oh0) * p.IWp + j * p.sw + p.ow0) *
+                                           p.Ctot + g * p.Cgp) * 6u;
+        float sum = EPI == 0 && !tail && p.bias ? p.bias[g * M + m] : 0.f;
+        for (int e0 = 0; e0 < nst - s_begin && sum == sum; ++e0) {
+            // from the window's centre on: the one place that is never padding
+            const int s = s_begin + (e0 + first_s) % (nst - s_begin);
+            u32x4 a[kStageU][3], b[kStageU][3];
+#pragma unroll
+            for (int e = 0; e < kStageU; ++e) {
+                const int kc = s * kStageU + e;
+                int tap, c8;
+                if constexpr (ORD == 2) {
+                    const int cb = (int)fdiv((uint32_t)s, p.div_ntap);
+                    tap = s - cb * p.ntap;
+                    c8 = cb * kStageU + e;
+                } else {
+                    tap = (int)fdiv((uint32_t)kc, p.div_cg8);
+                    c8 = kc - tap * p.Cg8;
+                }
+                const int u = (int)fdiv((uint32_t)tap, p.div_kw);
+                const int v = tap - u * p.kw;
+                const uint32_t oa = (uint32_t)((g * M + m) * p.Ru + kc) * (uint32_t)kUnit;
+                const uint32_t ob = at + (uint32_t)((u * p.IWp + v) * p.Ctot + 8 * c8) * 6u;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    a[e][t] = buf_ld_b128(ra, kc < p.KC ? oa + 16 * t : kOob);
+                    b[e][t] = buf_ld_b128(rx, kc < p.KC ? ob + 16 * t : kOob);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < kStageU; ++e)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int w = k / 2, sh = k % 2 * 16;
+                    sum = fmaf(x3_float(a[e][0][w] >> sh & 0xffffu, a[e][1][w] >> sh & 0xffffu,
+                                        a[e][2][w] >> sh & 0xffffu),
+                               x3_float(b[e][0][w] >> sh & 0xffffu, b[e][1][w] >> sh & 0xffffu,
+                                        b[e][2][w] >> sh & 0xffffu), sum);
+                }
+        }
+        if (EPI >= 2 || tail) {
+            const int c0 = EPI >= 2 ? 0 : p.tail_c0;
+            const int r0 = (EPI >= 2 ? split * p.G + g : split) * M;
+            buf_st_f32(sum, EPI >= 2 ? ry : make_rsrc(p.Pt, p.Pt_bytes),
+                       (uint32_t)((r0 + m) * (p.Ncol - c0) + col - c0) * 4u);
+        } else if constexpr (EPI == 0) {
+            buf_st_f32(sum > 0.f ? sum : (p.relu ? 0.f : sum), ry,
+                       (uint32_t)((n * p.Cout + g * M + m) * OHW + pix) * 4u);
+        } else if constexpr (EPI == 1) {
+            const int c = (int)fdiv((uint32_t)m, p.div_pss);
+            const int fr = m - c * p.psh * p.psw;
+            const int fh = (int)fdiv((uint32_t)fr, p.div_psw);
+            const int h = p.psh * (i + p.a0h) - p.oph + fh;
+            const int w = p.psw * (j + p.a0w) - p.opw + fr - fh * p.psw;
+            if ((unsigned)h >= (unsigned)p.OutH || (unsigned)w >= (unsigned)p.OutW)
+                continue;
+            const uint32_t off =
+                (uint32_t)(((n * p.Cout + g * p.Cg_out + c) * p.OutH + h) * p.OutW + w) * 4u;
+            if (MASK && !(p.Omask[off / 4] > 0.f))
+                sum = 0.f;
+            buf_st_f32(sum, ry, off);
+        }
+    } while (again);
 }
 
 // ----------------------------------------------------------- weight gradient
@@ -904,11 +1002,28 @@ conv_wgrad_x3_kernel(const WgradX3Params p)
     }
     mul(1, 0, 2);
     mul(1, 2, 0);
+    float odd = 0.f;  // (NaN once a sum is infinite or NaN)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < NI; ++ni) {
             acc[mi][ni] += lo[mi][ni];
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                odd = fmaf(acc[mi][ni][q], 0.f, odd);
+        }
+    static_assert(MI * NI * 16 <= 64, "one bit per output");
+    uint64_t again = 0;
+    if (__builtin_expect(odd != odd, 0)) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int q = 0; q < 16; ++q)
+                    again |= (uint64_t)!__builtin_isfinite(acc[mi][ni][q])
+                             << ((mi * NI + ni) * 16 + q);
+    }
 
     // partial result P[split][g*Kg + m][r], lanes along r
     const __amdgpu_buffer_rsrc_t rp = make_rsrc(p.P, p.P_bytes);
@@ -926,6 +1041,52 @@ conv_wgrad_x3_kernel(const WgradX3Params p)
                            ((uint32_t)(pbase + (g * p.Kg + m) * p.Rw + r) * 4u) | bad);
             }
     }
+
+    // sums that came out infinite or NaN, formed again in float arithmetic (see
+    // conv_gemm_x3_kernel)
+    if (__builtin_expect(again == 0, 1))
+        return;
+    __builtin_amdgcn_s_waitcnt(kVmcnt0);
+    do {
+        const int bit = __builtin_ctzll(again);
+        again &= again - 1;
+        const int blk = bit / 16;
+        const int m = m0 + wm * MI * MT + blk / NI * MT + MfmaX3<32>::row(bit % 16, lane);
+        const int r = r0 + wn * NI * MT + blk % NI * MT + (lane & 31);
+        if (m >= p.Kg || r >= p.Rw)
+            continue;
+        const int t = r / p.Cgp;
+        const int u = t / p.kw;
+        const int cd = g * p.Kgp + m, cx = g * p.Cgp + r - t * p.Cgp;
+        const uint32_t od = (uint32_t)(cd / 8 * kUnit + cd % 8 * 2);
+        const uint32_t ox = (uint32_t)((u * p.IWp + t - u * p.kw) * p.Ctot) * 6u +
+                            (uint32_t)(cx / 8 * kUnit + cx % 8 * 2);
+        float sum = 0.f;
+        for (int c = col_begin; c < col_end && sum == sum; c += 16) {
+            uint16_t d[16][3], x[16][3];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int n = (int)fdiv((uint32_t)(c + e), p.div_ohw);
+                const int pix = c + e - n * OHW;
+                const int i = (int)fdiv((uint32_t)pix, p.div_ow);
+                const int j = pix - i * p.OW;
+                const uint32_t ad =
+                    (uint32_t)(((n * p.DHp + i + p.dtb) * p.DWp + j + p.dlb) * p.Ktot) * 6u + od;
+                const uint32_t ax =
+                    (uint32_t)(((n * p.IHp + i * p.sh) * p.IWp + j * p.sw) * p.Ctot) * 6u + ox;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    d[e][k] = buf_ld_u16(rd, c + e < col_end ? ad + 16 * k : kOob);
+                    x[e][k] = buf_ld_u16(rx, c + e < col_end ? ax + 16 * k : kOob);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                sum = fmaf(x3_float(d[e][0], d[e][1], d[e][2]), x3_float(x[e][0], x[e][1], x[e][2]),
+                           sum);
+        }
+        buf_st_f32(sum, rp, (uint32_t)(pbase + (g * p.Kg + m) * p.Rw + r) * 4u);
+    } while (again);
 }
 
 // ------------------------------------------------------------------ staging

@@ -133,6 +133,66 @@ def test_terms_non_finite_as_float(overrides):
         assert ((a[f] - t[f]).abs() / scale).max() < 1e-3
 
 
+def _tile(overrides, tile, how):
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    overrides.setenv("CAFFE_X3_FWD_TILE", str(tile))
+    overrides.setenv("CAFFE_X3_DGRAD_TILE", str(tile))
+    overrides.setenv("CAFFE_X3_WGRAD_TILE", str(min(tile, 2)))
+    for k, v in how.items():
+        overrides.setenv(f"CAFFE_X3_{k}", str(v))
+
+
+SPLIT3 = {f"{k}_SPLITS": 3 for k in ("FWD", "DGRAD", "WGRAD")}
+TAIL2 = {"TAIL_SPLITS": 2, "TAIL_UNITS": 3}
+
+
+def _same_sign_close(got, ref, R, what):
+    """Sums of terms of one sign: infinite where the 64-bit sum is past the
+    largest float, else within one rounding a term (and two) of it."""
+    torch.cuda.synchronize()
+    got = got.double().cpu().numpy()
+    over = np.abs(ref) > 2.0 ** 128
+    assert np.array_equal(got[over], np.copysign(np.inf, ref[over])), what
+    err = np.abs(got[~over] - ref[~over])
+    bound = (R + 2) * 2.0 ** -24 * np.abs(ref[~over]) + 2.0 ** -149
+    assert np.all(err <= bound), f"{what}: {(err / bound).max():.2f} of the bound"
+    return over
+
+
+@pytest.mark.parametrize("tile", range(4))
+@pytest.mark.parametrize("how", [{}, SPLIT3, TAIL2], ids=["whole", "split", "tail"])
+@pytest.mark.parametrize("relu", [False, True])
+def test_terms_finite_products_overflow(overrides, tile, how, relu):
+    """Finite operands of which some products (2^137 and more: the small
+    products, whose signs are those of the rounding, overflow too) and some
+    sums are past the largest float: infinite as in float arithmetic, and the
+    sums beside them stay what they are.  All terms of a sum have one sign, so
+    the order of the additions decides nothing."""
+    _tile(overrides, tile, how)
+    c = (3, 64, 21, 19, 140, 3, 3, 1, 1, 1, 1, 2)
+    N, C, H, W, K, kh, kw, sh, sw, ph, pw, g = c
+    x, w, b, gd, top = _case(c)
+    rng = np.random.default_rng(137)
+    sign = np.where(np.arange(K) % 3 == 0, -1, 1).astype(np.float32)[:, None, None]
+    big = lambda a, n, v: np.where(rng.random(a.shape) < 1 / n, np.float32(v), np.float32(1))
+    x = np.abs(x) * big(x, 50, 1e30)
+    w = np.abs(w) * sign[..., None] * np.where(np.arange(K) % 5 < 2, np.float32(1e30),
+                                               np.float32(1))[:, None, None, None]
+    gd = np.abs(gd) * sign * big(gd, 4000, 3e25)
+    assert all(np.isfinite(a).all() for a in (x, w, gd))
+    y = cc.conv_forward(_t(x), _t(w), None, 1, 1, g, relu)
+    over = _same_sign_close(y, oracle.conv_forward(x, w, None, 1, 1, g, relu), 32 * 9, "forward")
+    assert 0.02 < over.mean() < 0.9
+    dx, dw, db = cc.conv_backward(_t(x), _t(w), _t(gd), _t(top), 1, 1, g, relu,
+                                  flags=cc.BACKWARD_MASK_BOTTOM_DIFF)
+    rx, rw, rb = oracle.conv_backward(x, w, gd, top=top, stride=1, pad=1, group=g, relu=relu)
+    for got, ref, R, what in ((dx, rx * (x > 0), 70 * 9, "data gradient"),
+                              (dw, rw, N * H * W, "weight gradient"),
+                              (db, rb, N * H * W, "bias gradient")):
+        over = _same_sign_close(got, ref, R, what)
+        assert what == "bias gradient" or 0.002 < over.mean() < 0.9, (what, over.mean())
+
+
 def test_terms_kept_bottom_and_weight_stream(overrides):
     """The forward's staging read by the backward, and the weight side on a
     stream of its own, give the same bits; a workspace of the minimum size
