@@ -134,11 +134,13 @@ size_t caffe_conv_workspace_bytes(const caffe_conv_desc* desc, int32_t pass);
 
 /* Bytes of workspace with which `pass` runs its fastest kernels (at least
  * caffe_conv_workspace_size).  Large CAFFE_F32 convolutions run on the bf16
- * matrix instructions, each float operand staged in the workspace as the exact
- * sum of three bf16 terms (products, sums and results keep float precision);
- * with a workspace of at least caffe_conv_workspace_size but less than this
- * they run on the float instructions, which stage nothing.  The two forms
- * differ by rounding.  Host-only. */
+ * matrix instructions, each float operand, subnormals included, staged in the
+ * workspace as the exact sum of three bf16 terms; a product loses at most 2^-24
+ * of itself, sums and results are float, and results that are infinite or NaN
+ * are formed in float arithmetic.  With a workspace of at least
+ * caffe_conv_workspace_size but less than this they run on the float
+ * instructions, which stage nothing.  The two forms differ by rounding.
+ * Host-only. */
 int caffe_conv_workspace_preferred(const caffe_conv_desc* desc, int32_t pass, size_t* bytes);
 
 /* 1 when `pass` (forward, data, weights, or backward: both gradients) runs on

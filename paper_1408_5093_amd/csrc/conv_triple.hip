@@ -5,14 +5,14 @@
 // this library reach 70-80% of it; the bf16 ones do sixteen times as much.  A
 // float has 24 significant bits and a bf16 eight, so x = x0 + x1 + x2 with
 // x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1 (each rounded to nearest
-// even) is exact (down to 2^-110, where the third term falls below bf16's
-// smallest), and
-//   x * y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) + O(2^-26 x y)
-// is six bf16 products, each exact in the float accumulator, at sixteen times
-// the rate.  The accumulator of the first products is rounded once per 16
-// reduction elements (32x32x16) instead of once per 2, the small products have
-// one of their own, and the sums come out closer to the 64-bit ones than the
-// float instructions' (conv2 at N = 256: forward 2.1e-7 of the norm against
+// even) is exact (see kScale for the smallest floats), and
+//   x * y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) + rest,
+// the rest at most 2^-24 of the product (2^-26.5 in the mean square), is six
+// bf16 products, each exact in the float accumulator, at sixteen times the
+// rate.  The accumulator of the first products is rounded once per 16 reduction
+// elements (32x32x16) instead of once per 2, the small products have one of
+// their own, and the sums come out closer to the 64-bit ones than the float
+// instructions' (conv2 at N = 256: forward 2.1e-7 of the norm against
 // 6.4e-7, data gradient 2.7e-7 / 6.6e-7, weight gradient 4.3e-7 / 5.1e-7).
 //
 // Measured at N = 256 (GEMM launches alone, us, float path -> here): conv2
@@ -46,9 +46,17 @@ constexpr int kRowC = 12;    // 16-byte chunks per operand row and stage
 // Slot of unit j within its term's four chunks of LDS row r: j ^ row_swz(r).
 __device__ __forceinline__ int row_swz(int r) { return (-(r >> 2)) & 3; }
 
-// A float that its first term can't stand for -- infinity, NaN, a finite value
-// that rounds to bf16's infinity -- is staged as this NaN and its own upper and
-// lower 16 bits.  The NaN reaches every output that the value enters, and such
+// Terms are those of 2^16 x: a float's last bit is 2^-149 or more and bf16's
+// smallest value 2^-133, so every float down to the subnormals is the exact sum
+// of its terms (unscaled, the third term was lost below 2^-110: an error of
+// 2^-16 at 2^-118, all of it at 2^-136).  The sums are divided by 2^32 at the
+// end.
+constexpr float kScale = 65536.f;
+constexpr float kUnscale = 1.f / (65536.f * 65536.f);
+
+// A float that its first term can't stand for -- infinity, NaN, from 2^112 (less
+// half a bf16 step) on -- is staged as this NaN and its own upper and lower 16
+// bits.  The NaN reaches every output that the value enters, and such
 // outputs are formed again in float arithmetic (x3_float, the end of both
 // kernels).
 constexpr uint32_t kMark = 0x7fc0;
@@ -56,14 +64,17 @@ constexpr uint32_t kMark = 0x7fc0;
 // The three bf16 terms of a pair of floats, packed (x low, y high).
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t t[3])
 {
+    const uint32_t ux = __builtin_bit_cast(uint32_t, x), uy = __builtin_bit_cast(uint32_t, y);
+    x *= kScale;
+    y *= kScale;
     t[0] = f32x2_to_bf16x2_rne(x, y);
     const float rx = x - __builtin_bit_cast(float, t[0] << 16);
     const float ry = y - __builtin_bit_cast(float, t[0] & 0xffff0000u);
     t[1] = f32x2_to_bf16x2_rne(rx, ry);
     t[2] = f32x2_to_bf16x2_rne(rx - __builtin_bit_cast(float, t[1] << 16),
                                ry - __builtin_bit_cast(float, t[1] & 0xffff0000u));
-    const uint32_t ux = __builtin_bit_cast(uint32_t, x), uy = __builtin_bit_cast(uint32_t, y);
-    const uint32_t ax = ux & 0x7fffffffu, ay = uy & 0x7fffffffu;
+    const uint32_t ax = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
+    const uint32_t ay = __builtin_bit_cast(uint32_t, y) & 0x7fffffffu;
     if (__builtin_expect((ax > ay ? ax : ay) >= 0x7f7f8000u, 0)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -84,7 +95,7 @@ __device__ __forceinline__ float x3_float(uint32_t t0, uint32_t t1, uint32_t t2)
 {
     const float sum = (__builtin_bit_cast(float, t0 << 16) + __builtin_bit_cast(float, t1 << 16)) +
                       __builtin_bit_cast(float, t2 << 16);
-    return t0 == kMark ? __builtin_bit_cast(float, (t1 << 16) | t2) : sum;
+    return t0 == kMark ? __builtin_bit_cast(float, (t1 << 16) | t2) : sum * (1 / kScale);
 }
 
 // Eight floats -> one unit (three 16-byte chunks at dst).
@@ -398,7 +409,7 @@ conv_gemm_x3_kernel(const GemmX3Params p)
 #pragma unroll
             for (int q = 0; q < Op::kRegs; ++q) {
                 const int m = m0 + wm * MI * MT + mi * MT + Op::row(q, lane);
-                init[q] = buf_ld_f32(rbias, m < M ? (uint32_t)(g * M + m) * 4u : kOob);
+                init[q] = buf_ld_f32(rbias, m < M ? (uint32_t)(g * M + m) * 4u : kOob) / kUnscale;
             }
         }
 #pragma unroll
@@ -534,7 +545,7 @@ conv_gemm_x3_kernel(const GemmX3Params p)
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            acc[mi][ni] += lo[mi][ni];
+            acc[mi][ni] = (acc[mi][ni] + lo[mi][ni]) * kUnscale;
 #pragma unroll
             for (int q = 0; q < Op::kRegs; ++q)
                 odd = fmaf(acc[mi][ni][q], 0.f, odd);
@@ -668,8 +679,8 @@ conv_gemm_x3_kernel(const GemmX3Params p)
     }
 
     // ---- sums that came out infinite or NaN, formed again in float
-    // arithmetic and stored over: an operand is no ordinary float, or a product
-    // overflows (the small products, of any sign, then overflow as well and
+    // arithmetic and stored over: an operand is no ordinary float, or a sum of
+    // 2^32 x y overflows, from x y about 2^96 on (the small products, of any sign, then overflow as well and
     // would make NaN of infinity).  A lane forms its outputs one after the
     // other, each until it is NaN: a path for blobs that are diverging (conv2's
     // forward at N = 64: 0.28 ms, with one infinity 3.5, all infinite 10, all
@@ -719,16 +730,19 @@ conv_gemm_x3_kernel(const GemmX3Params p)
                     b[e][t] = buf_ld_b128(rx, kc < p.KC ? ob + 16 * t : kOob);
                 }
             }
+            float part[kStageU] = {};  // (short chains of additions)
 #pragma unroll
             for (int e = 0; e < kStageU; ++e)
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     const int w = k / 2, sh = k % 2 * 16;
-                    sum = fmaf(x3_float(a[e][0][w] >> sh & 0xffffu, a[e][1][w] >> sh & 0xffffu,
-                                        a[e][2][w] >> sh & 0xffffu),
-                               x3_float(b[e][0][w] >> sh & 0xffffu, b[e][1][w] >> sh & 0xffffu,
-                                        b[e][2][w] >> sh & 0xffffu), sum);
+                    const float va = x3_float(a[e][0][w] >> sh & 0xffffu, a[e][1][w] >> sh & 0xffffu,
+                                              a[e][2][w] >> sh & 0xffffu);
+                    const float vb = x3_float(b[e][0][w] >> sh & 0xffffu, b[e][1][w] >> sh & 0xffffu,
+                                              b[e][2][w] >> sh & 0xffffu);
+                    part[e] = fmaf(va, vb, part[e]);
                 }
+            sum += (part[0] + part[1]) + (part[2] + part[3]);
         }
         if (EPI >= 2 || tail) {
             const int c0 = EPI >= 2 ? 0 : p.tail_c0;
@@ -1007,7 +1021,7 @@ conv_wgrad_x3_kernel(const WgradX3Params p)
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            acc[mi][ni] += lo[mi][ni];
+            acc[mi][ni] = (acc[mi][ni] + lo[mi][ni]) * kUnscale;
 #pragma unroll
             for (int q = 0; q < 16; ++q)
                 odd = fmaf(acc[mi][ni][q], 0.f, odd);
@@ -1080,10 +1094,12 @@ conv_wgrad_x3_kernel(const WgradX3Params p)
                     x[e][k] = buf_ld_u16(rx, c + e < col_end ? ax + 16 * k : kOob);
                 }
             }
+            float part[2] = {};
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                sum = fmaf(x3_float(d[e][0], d[e][1], d[e][2]), x3_float(x[e][0], x[e][1], x[e][2]),
-                           sum);
+                part[e & 1] = fmaf(x3_float(d[e][0], d[e][1], d[e][2]),
+                                   x3_float(x[e][0], x[e][1], x[e][2]), part[e & 1]);
+            sum += part[0] + part[1];
         }
         buf_st_f32(sum, rp, (uint32_t)(pbase + (g * p.Kg + m) * p.Rw + r) * 4u);
     } while (again);

@@ -193,6 +193,48 @@ def test_terms_finite_products_overflow(overrides, tile, how, relu):
         assert what == "bias gradient" or 0.002 < over.mean() < 0.9, (what, over.mean())
 
 
+@pytest.mark.parametrize("exp", [-112, -118, -126, -140])
+def test_terms_smallest_operands(overrides, exp):
+    """Operands down to the subnormals keep every bit (the other operand is
+    large, so that the results are ordinary floats)."""
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    c = (2, 40, 12, 9, 72, 3, 3, 1, 1, 1, 1, 2)
+    x, w, b, gd, top = _case(c)
+    up = np.float32(2.0 ** 90)
+    lo = [(a * np.float32(2.0 ** (exp + 100)) * np.float32(2.0 ** -100)) for a in (x, w, gd)]
+    hi = [a * up for a in (x, w, gd)]
+    assert all(0 < np.abs(a).max() < 2.0 ** (exp + 4) for a in lo)
+    for xs, ws in ((lo[0], hi[1]), (hi[0], lo[1])):
+        y = cc.conv_forward(_t(xs), _t(ws), None, 1, 1, 2, False)
+        _close(y, oracle.conv_forward(xs, ws, None, 1, 1, 2, False), 20 * 9, "forward")
+    for xs, ws, gs in ((hi[0], hi[1], lo[2]), (lo[0], lo[1], hi[2])):
+        dx, dw, _ = cc.conv_backward(_t(xs), _t(ws), _t(gs), _t(top), 1, 1, 2, True)
+        rx, rw, _ = oracle.conv_backward(xs, ws, gs, top=top, stride=1, pad=1, group=2, relu=True)
+        _close(dx, rx, 36 * 9, "data gradient")
+        _close(dw, rw, gd.size // 72, "weight gradient")
+
+
+def test_terms_infinity_times_subnormal_and_large_bias(overrides):
+    """inf * y is infinite for the smallest y, and a bias past the scaled
+    accumulators' range comes through."""
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    c = (1, 16, 9, 9, 24, 1, 1, 1, 1, 0, 0, 1)
+    x, w, b, _, _ = _case(c)
+    w[5] = 2.0 ** -149
+    w[6] = -2.0 ** -140
+    b[9], b[10] = 1e30, -3e38
+    x[0, 3, 4, 4] = np.inf
+    y = cc.conv_forward(_t(x), _t(w), _t(b), 1, 0, 1, False).cpu().numpy()
+    assert y[0, 5, 4, 4] == np.inf and y[0, 6, 4, 4] == -np.inf
+    x[0, 3, 4, 4] = 0
+    y[..., 4, 4] = 0
+    ref = oracle.conv_forward(x, w, b, 1, 0, 1, False)
+    ref[..., 4, 4] = 0
+    assert np.array_equal(y[0, 9:11], ref[0, 9:11].astype(np.float32))
+    keep = [k for k in range(24) if k not in (9, 10)]
+    _close(torch.from_numpy(y[:, keep]), ref[:, keep], 16, "beside the large biases")
+
+
 def test_terms_kept_bottom_and_weight_stream(overrides):
     """The forward's staging read by the backward, and the weight side on a
     stream of its own, give the same bits; a workspace of the minimum size
