@@ -235,6 +235,49 @@ def test_terms_infinity_times_subnormal_and_large_bias(overrides):
     _close(torch.from_numpy(y[:, keep]), ref[:, keep], 16, "beside the large biases")
 
 
+@pytest.mark.parametrize("mode", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("how", ["no relu", "relu", "masked"])
+@pytest.mark.parametrize("side", [False, True], ids=["one stream", "weight stream"])
+def test_terms_beside_float_passes(overrides, mode, how, side):
+    """Backward passes of which one gradient runs on terms and the other on the
+    float instructions (bits of the mode: 1 forward, 2 data, 4 weights), on a
+    workspace of garbage: each set of outputs, added to earlier gradients, on
+    a weight stream, with the forward's staging where it left one."""
+    overrides.setenv("CAFFE_CONV_X3", str(mode))
+    c = (3, 24, 13, 11, 40, 3, 3, 1, 1, 1, 1, 2)
+    relu = how != "no relu"
+    x, w, b, gd, top = _case(c, mode)
+    if how == "masked":
+        gd = gd * (top > 0)
+    flags = cc.BACKWARD_TOP_DIFF_MASKED if how == "masked" else 0
+    d = cc.conv_desc(x.shape, w.shape, 1, 1, 2, relu)
+    assert cc.conv_uses_terms(d, cc.PASS_BACKWARD_DATA) == (mode & 2 != 0)
+    assert cc.conv_uses_terms(d, cc.PASS_BACKWARD_WEIGHTS) == (mode & 4 != 0)
+    refs = oracle.conv_backward(x, w, gd, top=top if relu else None, stride=1, pad=1, group=2,
+                                relu=relu)
+    X, W, B, G, T = (_t(a) for a in (x, w, b, gd, top))
+    ws = torch.empty(max(cc.conv_workspace_preferred(d, p) for p in
+                         (cc.PASS_FORWARD, cc.PASS_BACKWARD)), dtype=torch.uint8, device=DEV)
+    stream = torch.cuda.Stream() if side else None
+    R = (20 * 9, gd.size // 40, gd.size // 40)
+    for want in ((1, 1, 1), (1, 1, 0), (1, 0, 1), (0, 1, 1), (0, 0, 1)):
+        for accumulate in (0, 1):
+            for kept in (0, cc.BACKWARD_BOTTOM_TERMS):
+                ws.fill_(0xFF)
+                if kept:
+                    cc.caffe_conv_forward(d, X, W, B, torch.empty_like(G), ws)
+                outs = [torch.full_like(a, 0.5 * accumulate) if on else None
+                        for a, on in zip((X, W, B), want)]
+                cc.caffe_conv_backward(d, G, T if relu and not flags else None,
+                                       X if want[1] else None, W if want[0] else None, *outs,
+                                       accumulate, flags | kept, ws, weight_stream=stream)
+                torch.cuda.synchronize()
+                for i, (o, ref) in enumerate(zip(outs, refs)):
+                    if o is not None:
+                        _close(o, ref + (0.5 * accumulate if i else 0), R[i],
+                               f"{want} accumulate {accumulate} kept {kept}: output {i}")
+
+
 def test_terms_kept_bottom_and_weight_stream(overrides):
     """The forward's staging read by the backward, and the weight side on a
     stream of its own, give the same bits; a workspace of the minimum size
