@@ -139,8 +139,11 @@ size_t caffe_conv_workspace_bytes(const caffe_conv_desc* desc, int32_t pass);
  * of itself, sums and results are float, and results that are infinite or NaN
  * are formed in float arithmetic.  With a workspace of at least
  * caffe_conv_workspace_size but less than this they run on the float
- * instructions, which stage nothing.  The two forms differ by rounding.
- * Host-only. */
+ * instructions, which stage nothing.  Where the float kernels' split partials
+ * need as much as the staging, the two sizes are equal and the terms always
+ * run, in caffe_conv_forward_noalloc too.  The two forms differ by rounding; so
+ * may the weight gradient of a call for both gradients and of a call for the
+ * weights alone, which decide for themselves.  Host-only. */
 int caffe_conv_workspace_preferred(const caffe_conv_desc* desc, int32_t pass, size_t* bytes);
 
 /* 1 when `pass` (forward, data, weights, or backward: both gradients) runs on

@@ -9,6 +9,8 @@ at most the result's size in the mean, so the 2-norm error is about
 2^-24 sqrt(R / 16) of the result's norm plus the last rounding.  A missing
 product of any order (2^-9, 2^-18 of a term) is above it.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -312,3 +314,25 @@ def test_terms_kept_bottom_and_weight_stream(overrides):
     got = run(least[0], cc.BACKWARD_BOTTOM_TERMS, None, True, least[1])  # (no effect there)
     overrides.setenv("CAFFE_CONV_X3", "0")
     assert all(torch.equal(a, t) for a, t in zip(run(least[0], fwd=least[1]), got))
+
+
+def test_terms_where_the_least_workspace_holds_them():
+    """A layer whose float split partials need as much workspace as the staging:
+    its least workspace is the preferred one, and every forward call, the one
+    on the static scratch too, runs on terms."""
+    N, C, H, W, K, k = 3, 54, 27, 17, 478, 3
+    x, w, b, _, _ = _case((N, C, H, W, K, k, k, 1, 1, 1, 1, 1))
+    d = cc.conv_desc(x.shape, w.shape, 1, 1, 1, True)
+    need = cc.conv_workspace_size(d, cc.PASS_FORWARD)
+    assert cc.conv_uses_terms(d, cc.PASS_FORWARD)
+    assert need == cc.conv_workspace_preferred(d, cc.PASS_FORWARD) <= cc.NOALLOC_SCRATCH_BYTES
+    X, Wt, B = _t(x), _t(w), _t(b)
+    y = torch.empty((N, K, H, W), device=DEV)
+    cc.caffe_conv_forward(d, X, Wt, B, y, torch.empty(need, dtype=torch.uint8, device=DEV))
+    _close(y, oracle.conv_forward(x, w, b, 1, 1, 1, True), C * k * k, "forward")
+    z = torch.empty_like(y)
+    cc.check(cc.load().caffe_conv_forward_noalloc(
+        ctypes.byref(d), *(ctypes.c_void_p(t.data_ptr()) for t in (X, Wt, B, z)),
+        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    torch.cuda.synchronize()
+    assert torch.equal(y, z)
