@@ -46,8 +46,9 @@
  * device memory of the current device), allocated and owned by the caller,
  * 16-byte aligned.  The library never allocates, frees or retains caller
  * memory.  Scratch space comes from the caller as `workspace` / `ws_bytes`
- * (device memory, 256-byte aligned); query the size with
- * caffe_conv_workspace_size().  No tensor may exceed 2^31 - 1 bytes.
+ * (device memory, 256-byte aligned); query the least size with
+ * caffe_conv_workspace_size() and the one with which a pass runs its fastest
+ * kernels with caffe_conv_workspace_preferred().  No tensor may exceed 2^31 - 1 bytes.
  *
  * Execution.  Every compute call only validates its arguments on the host
  * and enqueues kernels on `stream` (a hipStream_t; NULL = the default
@@ -71,9 +72,10 @@
  *
  * Tuning.  Tile shapes, split counts and kernel variants are chosen from the
  * descriptor, and between float and three-term operands also by the workspace
- * given (caffe_conv_workspace_preferred).  Environment variables named CAFFE_CONV_*, CAFFE_FC_*,
- * CAFFE_BF16_* and CAFFE_BACKWARD_FORK override those choices for profiling
- * and tests, and are read only while CAFFE_PROFILE_OVERRIDES=1 is set.
+ * given (caffe_conv_workspace_preferred).  Environment variables named
+ * CAFFE_CONV_*, CAFFE_FC_*, CAFFE_BF16_*, CAFFE_X3_* and CAFFE_BACKWARD_FORK
+ * override those choices for profiling and tests, and are read only while
+ * CAFFE_PROFILE_OVERRIDES=1 is set.
  */
 #ifndef CAFFE_CONV_H
 #define CAFFE_CONV_H
@@ -133,8 +135,9 @@ int caffe_conv_workspace_size(const caffe_conv_desc* desc, int32_t pass, size_t*
 size_t caffe_conv_workspace_bytes(const caffe_conv_desc* desc, int32_t pass);
 
 /* Bytes of workspace with which `pass` runs its fastest kernels (at least
- * caffe_conv_workspace_size).  Large CAFFE_F32 convolutions run on the bf16
- * matrix instructions, each float operand, subnormals included, staged in the
+ * caffe_conv_workspace_size).  Large CAFFE_F32 convolutions (rows of at most
+ * 256 pixels, W and Wo, their staging's limit) run on the bf16 matrix
+ * instructions, each float operand, subnormals included, staged in the
  * workspace as the exact sum of three bf16 terms; a product loses at most 2^-24
  * of itself, sums and results are float, and results that are infinite or NaN
  * are formed in float arithmetic.  With a workspace of at least

@@ -562,7 +562,7 @@ int plan_bf16(ConvPlan* p)
             }
         }
     }
-    q.wgrad_xcd_order = env_tile("CAFFE_BF16_WGRAD_UNIT_ORDER") != 0;
+    q.wgrad_xcd_order = env_tile("CAFFE_BF16_WGRAD_XCD_ORDER") != 0;
     splits = std::max<int64_t>(1, std::min(splits, max_splits));
     int64_t cps = (ncol + splits - 1) / splits;
     cps = std::max<int64_t>(tk, (cps + tk - 1) / tk * tk);

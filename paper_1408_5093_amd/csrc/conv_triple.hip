@@ -98,7 +98,6 @@ __device__ __forceinline__ float x3_float(uint32_t t0, uint32_t t1, uint32_t t2)
     return t0 == kMark ? __builtin_bit_cast(float, (t1 << 16) | t2) : sum * (1 / kScale);
 }
 
-// Eight floats -> one unit (three 16-byte chunks at dst).
 // The three terms of eight floats, a 16-byte chunk each.
 __device__ __forceinline__ void unit_terms(const float v[8], u32x4 o[3])
 {
@@ -112,6 +111,7 @@ __device__ __forceinline__ void unit_terms(const float v[8], u32x4 o[3])
     }
 }
 
+// Eight floats -> one unit (three 16-byte chunks at dst).
 __device__ __forceinline__ void store_unit(const float v[8], bf16_t* dst)
 {
     u32x4 o[3];
@@ -394,8 +394,8 @@ conv_gemm_x3_kernel(const GemmX3Params p)
         }
     };
 
-    // forward: accumulators start at the bias of their row (a tail split's
-    // partials leave the bias to the reduce)
+    // Forward: accumulators start at the bias of their row (a tail split's
+    // partials leave the bias to the reduce).
     // The products of the two first terms add up in acc, the other five, 2^-8
     // of them and less, in lo: acc is rounded once per instruction depth, not
     // six times.

@@ -559,17 +559,17 @@ def test_caffenet_bf16_step_lrn_staging_matches():
 
 @pytest.mark.parametrize("case", [
     # N, C, H, W, K, k, pad, group, blocks (the split target; 0: the default)
-    (4, 256, 13, 13, 128, 3, 1, 1, 0),     # one split: one unit, seven empty ones exit
-    (48, 256, 13, 13, 256, 3, 1, 2, 72),   # 2 groups x 8 splits: two units per XCD
-    (24, 256, 13, 11, 192, 3, 1, 2, 108),  # 96-row tiles, 2 groups x 6 splits, ragged
+    (4, 256, 13, 13, 128, 3, 1, 1, 0),     # one split of 9 tiles: runs of two, of one and empty
+    (48, 256, 13, 13, 256, 3, 1, 2, 72),   # 2 groups x 8 splits x 5 tiles: a run of ten per XCD
+    (24, 256, 13, 11, 192, 3, 1, 2, 108),  # 96-row tiles, 2 groups x 11 splits x 5: a ragged run
 ])
-def test_wgrad_unit_order_bf16(case, overrides):
-    """The bf16 weight gradient with each (group, split) unit's tiles on one
-    XCD against the linear tile order at the same split count: the same
-    partial sums in the same order, so the same bits; and the oracle on the
-    rounded operands."""
+def test_wgrad_xcd_order_bf16(case, overrides):
+    """The bf16 weight gradient with a contiguous run of tiles on each XCD
+    against the linear tile order at the same split count: the same partial
+    sums in the same order, so the same bits; and the oracle on the rounded
+    operands."""
     N, C, H, W, K, k, pad, g, blocks = case
-    print(f"bf16 wgrad unit order {case}", flush=True)
+    print(f"bf16 wgrad XCD order {case}", flush=True)
     rng = np.random.default_rng([79, *case])
     xr = wl.round_bf16(rng.standard_normal((N, C, H, W)).astype(np.float32))
     wr = wl.round_bf16((rng.standard_normal((K, C // g, k, k)) * 0.2).astype(np.float32))
@@ -580,7 +580,7 @@ def test_wgrad_unit_order_bf16(case, overrides):
         overrides.setenv("CAFFE_CONV_WGRAD_BLOCKS", str(blocks))
     dws = []
     for order in ("1", "0"):
-        overrides.setenv("CAFFE_BF16_WGRAD_UNIT_ORDER", order)
+        overrides.setenv("CAFFE_BF16_WGRAD_XCD_ORDER", order)
         _, dw, _ = cc.conv_backward(xb, wb, _t(gd), None, 1, pad, g, need=("dw",))
         torch.cuda.synchronize()
         dws.append(dw)
