@@ -226,9 +226,9 @@ enum caffe_backward_flags {
      * training-step order: forward, then backward on a workspace of its
      * own).  The weight gradient then reads that copy instead of staging
      * bottom again; the staged copy sits at the start of both passes'
-     * workspaces.  No effect in CAFFE_F32 mode, which stages nothing; a
-     * workspace that does not hold the forward's copy gives a wrong
-     * weight gradient. */
+     * workspaces.  No effect in CAFFE_F32 mode (see
+     * CAFFE_BACKWARD_BOTTOM_TERMS); a workspace that does not hold the
+     * forward's copy gives a wrong weight gradient. */
     CAFFE_BACKWARD_BOTTOM_STAGED = 4,
     /* bf16 modes: the workspace holds this layer's staged top gradient and
      * its bias-gradient partial sums, written by the layer above's
@@ -243,8 +243,10 @@ enum caffe_backward_flags {
     /* CAFFE_F32 mode: as CAFFE_BACKWARD_BOTTOM_STAGED for the three-term
      * staging of bottom (caffe_conv_workspace_preferred) that the last
      * caffe_conv_forward with the same descriptor, bottom, workspace and
-     * ws_bytes left in the workspace, nothing of which has changed since.
-     * No effect where either pass runs on the float instructions. */
+     * ws_bytes left in the workspace, nothing of which has changed since
+     * (no effect where either pass runs on the float instructions); and in
+     * caffe_conv_backward_ex a weight gradient on three-term operands runs on
+     * weight_stream. */
     CAFFE_BACKWARD_BOTTOM_TERMS = 64
 };
 
@@ -273,11 +275,12 @@ int caffe_conv_backward(const caffe_conv_desc* desc, const float* top_diff, cons
  * while `stream` goes on with the data gradient (bottom_diff, ordered on
  * `stream`); nothing joins the two streams, so a network can run one
  * layer's weight gradient beside the next layers' data gradients and glue.
- * In CAFFE_F32 mode both passes share the workspace's partial sums and run
- * on `stream`, which weight_stream then waits for.  The workspace stays in
- * use until both streams have passed the call's work; the caller joins the
- * streams before reusing it or reading weight_diff on `stream`.  The
- * default-priority stream rule of the backward's auxiliary stream applies
+ * In CAFFE_F32 mode both passes run on `stream`, which weight_stream then
+ * waits for, unless the weight gradient runs on three-term operands and flags
+ * has CAFFE_BACKWARD_BOTTOM_TERMS: then as in the bf16 modes.  The workspace
+ * stays in use until both streams have passed the call's work; the caller
+ * joins the streams before reusing it or reading weight_diff on `stream`.
+ * The default-priority stream rule of the backward's auxiliary stream applies
  * to weight_stream as well. */
 int caffe_conv_backward_ex(const caffe_conv_desc* desc, const float* top_diff, const float* top,
                            const void* bottom, const void* weight, float* bottom_diff,

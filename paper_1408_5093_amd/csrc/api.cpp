@@ -1852,11 +1852,12 @@ int backward_bf16_staged(const ConvPlan& q, const float* sums, int terms, bool m
 // The float backward with its data gradient (xd) and / or weight gradient (xw)
 // on three bf16 terms: the masked top gradient is staged once for both; a
 // pass that stays on the float instructions runs on `s` as before.  The
-// weight side goes to wst (when given) only if it is the three-term one.
+// weight side goes to wst (when given) only if it is the three-term one and
+// the caller knows of it (`beside`); else wst waits for s.
 int backward_x3(const ConvPlan& q, const float* top_diff, const float* top, bool masked,
                 bool mask_bottom, bool kept, const float* bottom, const float* weight, float* bottom_diff,
                 float* weight_diff, float* bias_diff, int accumulate, bool xd, bool xw, char* ws,
-                hipStream_t s, hipStream_t wst)
+                hipStream_t s, hipStream_t wst, bool beside)
 {
     const ConvPlan::X3& x = q.x3;
     const bool relu = q.relu && !masked;
@@ -1875,7 +1876,7 @@ int backward_x3(const ConvPlan& q, const float* top_diff, const float* top, bool
                "ReLU backward launch");
         dsrc = D;
     }
-    hipStream_t sw = xw && wst ? wst : s;
+    hipStream_t sw = xw && wst && beside ? wst : s;
     if (sw != s)
         CHECK(stream_follow(sw, s));
     if (xd)
@@ -2156,11 +2157,11 @@ int backward_impl(const caffe_conv_desc* desc, const float* top_diff, const floa
     const bool xw = (q.x3.wgt || (xd && q.x3.wgt_joint)) && weight_diff && x3_ws;
     if (xd || xw) {
         // the forward's staging of bottom, where it ran on this workspace
-        const bool kept = (flags & CAFFE_BACKWARD_BOTTOM_TERMS) != 0 && q.x3.fwd &&
-                          ws_bytes >= q.x3.ws_fwd;
+        const bool terms = (flags & CAFFE_BACKWARD_BOTTOM_TERMS) != 0;
+        const bool kept = terms && q.x3.fwd && ws_bytes >= q.x3.ws_fwd;
         return backward_x3(q, top_diff, top, masked, mask_bottom, kept, (const float*)bottom,
                            (const float*)weight, bottom_diff, weight_diff, bias_diff, accumulate,
-                           xd, xw, ws, s, wst);
+                           xd, xw, ws, s, wst, terms);
     }
     const float* dsrc = top_diff;
     if (q.relu && !masked && (bottom_diff || weight_diff) && q.top_elems > 0) {

@@ -280,6 +280,30 @@ def test_terms_beside_float_passes(overrides, mode, how, side):
                                f"{want} accumulate {accumulate} kept {kept}: output {i}")
 
 
+def test_terms_weight_side_stays_on_stream_unasked(overrides):
+    """A float backward with a weight stream keeps its weight side on the main
+    stream, as it did before there were terms, unless the call names them
+    (BACKWARD_BOTTOM_TERMS): behind a weight stream that is busy the gradients
+    are there on the main stream without a join."""
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    c = (4, 32, 14, 13, 72, 5, 5, 1, 1, 2, 2, 1)
+    x, w, b, gd, top = (_t(a) for a in _case(c))
+    d = cc.conv_desc(x.shape, w.shape, 1, 2, 1, True)
+    ws = torch.empty(cc.conv_workspace_preferred(d, cc.PASS_BACKWARD), dtype=torch.uint8,
+                     device=DEV)
+    ref = [torch.empty_like(a) for a in (x, w, b)]
+    cc.caffe_conv_backward(d, gd, top, x, w, *ref, 0, 0, ws)
+    outs = [torch.full_like(a, float("nan")) for a in (x, w, b)]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(10_000_000)
+    cc.caffe_conv_backward(d, gd, top, x, w, *outs, 0, 0, ws, weight_stream=side)
+    got = [a.clone() for a in outs]  # on the main stream, not joined
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, t) for a, t in zip(ref, got))
+
+
 def test_terms_kept_bottom_and_weight_stream(overrides):
     """The forward's staging read by the backward, and the weight side on a
     stream of its own, give the same bits; a workspace of the minimum size
