@@ -7,7 +7,10 @@ in another; the splits' partials and the bias add a few roundings more.  For
 operands of random sign these roundings are independent and the running sum is
 at most the result's size in the mean, so the 2-norm error is about
 2^-24 sqrt(R / 16) of the result's norm plus the last rounding.  A missing
-product of any order (2^-9, 2^-18 of a term) is above it.
+product of any order (2^-9, 2^-18 of a term) is above it.  Each single output is
+within its worst case: the two accumulators' R / 16 additions and a few more,
+each off by at most 2^-23 (the instructions may cut instead of rounding) of the
+sum of the terms' sizes, and each product by 2^-24.
 """
 import ctypes
 
@@ -34,6 +37,14 @@ def _close(got, ref, R, what):
     rel = np.linalg.norm(got - ref) / max(np.linalg.norm(ref), 1e-300)
     bound = (2 + np.sqrt(R / 16)) * 2.0 ** -24
     assert rel <= bound, f"{what}: {rel:.2e} > {bound:.2e}"
+
+
+def _each(got, ref, sizes, R, what):
+    """sizes: the same sum over the absolute values of its terms."""
+    torch.cuda.synchronize()
+    err = np.abs(got.double().cpu().numpy() - ref)
+    bound = (R / 16 + 8) * 2.0 ** -23 * sizes + 2.0 ** -149
+    assert np.all(err <= bound), f"{what}: an output is off by {(err / bound).max():.2f} bounds"
 
 
 def _case(c, seed=0):
@@ -71,13 +82,21 @@ def test_terms_parity(overrides, c, relu):
     x, w, b, gd, top = _case(c)
     R = (C // g) * kh * kw
     y = cc.conv_forward(_t(x), _t(w), _t(b), (sh, sw), (ph, pw), g, relu)
-    _close(y, oracle.conv_forward(x, w, b, (sh, sw), (ph, pw), g, relu), R, "forward")
+    ref = oracle.conv_forward(x, w, b, (sh, sw), (ph, pw), g, relu)
+    _close(y, ref, R, "forward")
+    ax, aw, agd = (np.abs(a) for a in (x, w, gd))
+    _each(y, ref, oracle.conv_forward(ax, aw, np.abs(b), (sh, sw), (ph, pw), g, False), R,
+          "forward")
     dx, dw, db = cc.conv_backward(_t(x), _t(w), _t(gd), _t(top), (sh, sw), (ph, pw), g, relu)
     rx, rw, rb = oracle.conv_backward(x, w, gd, top=top, stride=(sh, sw), pad=(ph, pw), group=g,
                                       relu=relu)
     _close(dx, rx, (K // g) * kh * kw, "data gradient")
     _close(dw, rw, gd.size // K, "weight gradient")
     _close(db, rb, gd.size // K, "bias gradient")
+    sx, sw_, _ = oracle.conv_backward(ax, aw, agd, top=top, stride=(sh, sw), pad=(ph, pw), group=g,
+                                      relu=relu)
+    _each(dx, rx, sx, (K // g) * kh * kw, "data gradient")
+    _each(dw, rw, sw_, gd.size // K, "weight gradient")
 
 
 @pytest.mark.parametrize("tile", range(4))
@@ -107,10 +126,12 @@ def test_terms_tiles_and_splits(overrides, tile, how):
     _close(dw, rw, N * H * W, "weight gradient")
 
 
-def test_terms_non_finite_as_float(overrides):
+@pytest.mark.parametrize("stride", [1, 2])
+def test_terms_non_finite_as_float(overrides, stride):
     """Infinities, NaN and the largest floats give what the float kernels
-    give, element by element."""
-    c = (2, 48, 11, 12, 40, 3, 3, 1, 1, 1, 1, 2)
+    give, element by element (with a stride the data gradient's phases have
+    taps that don't exist, zeros in both paths)."""
+    c = (2, 48, 11, 12, 40, 3, 3, stride, stride, 1, 1, 2)
     x, w, b, gd, top = _case(c)
     x[0, 3, 2, 5], x[0, 30, 9, 9], x[1, 4, 4, 4] = np.inf, -np.inf, np.nan
     x[1, 7, 10, 0], x[0, 9, 0, 0] = 3.4e38, 0.0
@@ -122,8 +143,9 @@ def test_terms_non_finite_as_float(overrides):
     for mode in ("0", "7"):
         overrides.setenv("CAFFE_CONV_X3", mode)
         with np.errstate(all="ignore"):
-            y = cc.conv_forward(_t(x), _t(w), _t(b), 1, 1, 2, False)
-            outs.append([y] + list(cc.conv_backward(_t(x), _t(w), _t(gd), None, 1, 1, 2, False)))
+            y = cc.conv_forward(_t(x), _t(w), _t(b), stride, 1, 2, False)
+            outs.append([y] + list(cc.conv_backward(_t(x), _t(w), _t(gd), None, stride, 1, 2,
+                                                    False)))
     torch.cuda.synchronize()
     for a, t in zip(*outs):
         assert torch.equal(torch.isnan(a), torch.isnan(t))
@@ -338,6 +360,33 @@ def test_terms_kept_bottom_and_weight_stream(overrides):
     got = run(least[0], cc.BACKWARD_BOTTOM_TERMS, None, True, least[1])  # (no effect there)
     overrides.setenv("CAFFE_CONV_X3", "0")
     assert all(torch.equal(a, t) for a, t in zip(run(least[0], fwd=least[1]), got))
+
+
+def test_terms_at_the_offsets_limit(overrides):
+    """Both stagings just below 2^31 bytes (one image more and the layer stays
+    on the float instructions): the first and last images' forward and data
+    gradient and, from a top gradient that is zero in all images but those, the
+    weight gradient."""
+    overrides.setenv("CAFFE_CONV_X3", "7")
+    C, H, N = 64, 56, (2 ** 31 - 1) // (58 * 58 * 64 * 6)
+    desc = lambda n: cc.conv_desc((n, C, H, H), (C, C, 3, 3), 1, 1, 1, False)
+    for p in (cc.PASS_FORWARD, cc.PASS_BACKWARD_DATA, cc.PASS_BACKWARD_WEIGHTS):
+        assert cc.conv_uses_terms(desc(N), p) and not cc.conv_uses_terms(desc(N + 1), p)
+    gen = torch.Generator(device=DEV).manual_seed(31)
+    x = torch.randn((N, C, H, H), generator=gen, device=DEV)
+    w = torch.randn((C, C, 3, 3), generator=gen, device=DEV) * 0.3
+    ends = [0, 1, N - 2, N - 1]
+    gd = torch.zeros_like(x)
+    gd[ends] = torch.randn((4, C, H, H), generator=gen, device=DEV)
+    y = cc.conv_forward(x, w, None, 1, 1)
+    xs, gs, ws = (a.cpu().numpy() for a in (x[ends], gd[ends], w))
+    _close(y[ends], oracle.conv_forward(xs, ws, None, 1, 1), C * 9, "forward")
+    del y
+    dx, dw, _ = cc.conv_backward(x, w, gd, None, 1, 1)
+    rx, rw, _ = oracle.conv_backward(xs, ws, gs, stride=1, pad=1)
+    _close(dx[ends], rx, C * 9, "data gradient")
+    assert not dx[2:-2].any()
+    _close(dw, rw, 4 * H * H, "weight gradient")
 
 
 def test_terms_where_the_least_workspace_holds_them():
