@@ -435,7 +435,7 @@ def forward_only(cc, layers, inputs, steps, warmup, stream, N):
         w = torch.from_numpy(inp["W"]).cuda()
         b = torch.from_numpy(inp["b"]).cuda()
         y = torch.empty((N, L.K, Ho, Wo), device="cuda")
-        ws = cc.Workspace().get(cc.conv_workspace_size(d, cc.PASS_FORWARD))
+        ws = cc.Workspace().get(cc.conv_workspace_preferred(d, cc.PASS_FORWARD))
 
         def call():
             cc.caffe_conv_forward(d, x, w, b, y, ws, stream)
@@ -444,7 +444,7 @@ def forward_only(cc, layers, inputs, steps, warmup, stream, N):
             call()
         ms, _, _, _ = timed_steps(call, stream, steps)
         flops = L.flops(N)
-        per[L.name] = {"ms": ms, "tflops": flops / (ms * 1e-3) / 1e12,
+        per[L.name] = {"kernel": kernel_of("fwd", L, N, False), "ms": ms, "tflops": flops / (ms * 1e-3) / 1e12,
                        "pct_mfma_peak": 100.0 * flops / (ms * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS}
         total_ms += ms
         total_flops += flops
