@@ -19,9 +19,10 @@
 // forward 890 -> 544, data gradient 937 -> 647, weight gradient 944 -> 525;
 // conv3 628 -> 321, 620 -> 311, 630 -> 330; conv4 491 -> 266, 496 -> 256, 492 ->
 // 282; conv5 318 -> 171, 341 -> 181, 323 -> 182.  That is 1.06-1.48 PFLOP/s of
-// bf16 products.  What bounds it is power: at 73% matrix-unit busy the clock
-// falls to 1.8-1.9 GHz (a stream kernel runs at 2.5), so a busier pipeline
-// gains less than its share.
+// bf16 products.  The matrix units are 47-72% busy (counters), at a clock that
+// falls as they get busier: conv2's data gradient 47% at 2.30 GHz, conv3's
+// forward 72% at 1.83, where the float kernels hold 2.4 GHz at 70%.  A busier
+// pipeline so gains less than its share.
 //
 // Operand staging.  Each operand is first rewritten in the workspace as
 // channel-contiguous units of 8 channels x 3 terms (48 bytes):
