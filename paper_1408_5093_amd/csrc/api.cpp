@@ -659,14 +659,55 @@ void plan_x3(ConvPlan* p, double est_f, double est_d, double est_w)
     x.RuF = (int)ruf;
     x.RuD = (int)rud;
     x.Rw = (int)rw;
-    // (shapes too small for any pass to gain, by the rule below without its
-    // GEMM term, are not planned further)
+    // Which path is faster: both paths' times as the plans' modelled GEMM times,
+    // launches and bytes, fitted to every pass of 14700 drawn layers of 0.01 to 80
+    // GFLOP, 1 to 16 groups, kernels 1 to 11, strides 1 to 4, timed on both.
+    // Terms: a GEMM runs at 0.55-1 of its modelled time, the small tiles at the
+    // long end; whole 32-channel stages help, a staging of over 160 MB leaves
+    // the caches, and the 48-row tile's taps of more than 80 channels that
+    // aren't whole stages read their pixels from beyond the L2; narrow groups'
+    // pixels waste half a line each.  Float: reductions of whole 16-channel
+    // taps run near their model, ragged ones at 1.2 of it, at 1.6-1.85 where
+    // padding is tested.  The fits are within 7% at the quartiles and 20% at
+    // the 5th and 95th percentiles, so that a pass takes the terms only with an
+    // eighth to spare.  Of the 12300 passes that so take them 0.9% measured more
+    // than 2% slower than on the float path, 22 more than 10% (up to 1.7x); with
+    // the fit to 61 layers that stood here before, 3.3% and 173, e.g. the
+    // forward of 494 images of 200 channels of 37 x 21 to 28, 7 x 7, stride 2, 4
+    // groups: 578 us float, 919 terms.  A sixth more passes take them.
     const double us = 1e-6, bx = (double)q.bottom_elems * 4, bt = (double)q.top_elems * 4;
-    const double of_f = 22 * us + (bx + xb) * 2.75e-13, of_d = 21 * us + (bt + db) * 2.7e-13;
-    const double of_w = 21 * us + (2 * bt + db) * 2.1e-13 + (bx + xb) * 3e-13;
-    const double float_f = 0.88 * (14 * us + 1.25 * est_f), float_d = 0.95 * (19 * us + 1.37 * est_d);
-    const double float_w = 0.95 * (18 * us + 0.87 * est_w + bt * 5.9e-13);
-    if (forced < 0 && of_f >= float_f && of_d >= float_d && of_w >= float_w)
+    const bool taps_d = q.Th * q.Tw > 1;
+    const double waste_x = q.G > 1 ? 64.0 / (x.Cgp * 6) : 0.0;
+    const double waste_d = q.G > 1 ? 64.0 / (x.Kgp * 6) : 0.0;
+    const double mask = q.relu ? 7 * us + bt * 0.64e-12 : 0.0;
+    const double masked = q.relu ? 2 * bt : bt;
+    const double of_f = 14.4 * us + (0.36 * xb * (1 + waste_x) + 0.2 * bt + 0.57 * wpb) * 1e-12;
+    const double of_d = 15.3 * us + (0.12 * masked + 0.36 * db * (1 + 1.4 * waste_d) + 0.32 * bx +
+                                   0.45 * wtb) * 1e-12;
+    const double of_w = 16.3 * us + (0.127 * bx + 0.19 * (double)(xb + db) + 0.22 * masked +
+                                     0.07 * (waste_x * xb + waste_d * db) + 14.4 * rw * q.K) * 1e-12;
+    // (the staging of D, which the two gradients of one call share)
+    const double share = 7 * us + (0.217 * db + 0.184 * masked) * 1e-12;
+    const double float_f = 12.8 * us + (0.03 * bx + 0.1 * bt + 0.9 * wpb) * 1e-12 +
+                           est_f * (q.fwd_tap              ? 1.07
+                                    : q.ph + q.pw == 0     ? 1.18
+                                    : q.Kg <= 48           ? 1.85
+                                                           : 1.6);
+    const double float_d = 13.3 * us + (0.31 * bx + 0.85 * wtb) * 1e-12 +
+                           (q.relu ? bt * 0.65e-12 : 0.0) +
+                           est_d * (q.dgrad_tap ? !taps_d ? 0.75 : q.Mt <= 48 ? 1.15 : 1.05
+                                    : !taps_d   ? 1.42
+                                    : q.Mt <= 48 ? 1.86
+                                                 : 1.62);
+    const double float_w = 15.4 * us + 0.03e-12 * bx + (q.relu ? bt * 0.69e-12 : 0.0) +
+                           est_w * ((q.wgrad_quad ? q.Kg <= 48 ? 1.06 : 0.93
+                                                  : q.Kg <= 48 ? 1.23 : 1.01) +
+                                    (q.splits <= 4 ? 0.16 : 0.0));
+    const double spare_f = 0.88, spare_d = 0.87, spare_w = 0.87, spare_j = 0.95, spare_m = 0.97;
+    // (layers too small for any pass to gain, whatever its GEMM takes, are not
+    // planned further)
+    if (forced < 0 && of_f >= spare_f * float_f && of_d >= spare_d * float_d &&
+        of_w >= spare_w * float_w)
         return;
     // one workgroup-stage (32 channels, six products) at the rate a unit
     // reaches
@@ -747,19 +788,28 @@ void plan_x3(ConvPlan* p, double est_f, double est_d, double est_w)
     x.splits = (int)splits;
     x.cols_per_split = (int)cps;
 
-    // Which path is faster: both paths' times were fitted (launches, the
-    // plans' modelled GEMM time, staged bytes) to calls measured on 61
-    // shapes, CaffeNet's at N = 4 .. 64 and drawn ones of 0.3 to 60 GFLOP: the
-    // fits are within 6-17% in the mean, and no shape they choose the terms
-    // for measured slower on them (e.g. forward of 13 x 13, 192 -> 192
-    // channels: N = 4 31 us float / 35 terms, N = 16 66 / 43, N = 64 176 / 98;
-    // 1 x 1 kernels, little work per staged byte, 36 / 59).  The weight
-    // gradient of a call that also forms the data gradient shares its staged
-    // top gradient (wgt_joint).
-    const bool f = of_f + 0.62 * tx_f < float_f;
-    const bool d = of_d + 0.76 * tx_d < float_d;
-    const bool w = of_w + 0.64 * tx_w < float_w;
-    const bool wj = 10 * us + 0.64 * tx_w + (bx + xb) * 3e-13 < 0.95 * (10 * us + 0.87 * est_w);
+    auto gemm = [&](int tile, int red, int taps, int64_t staged, bool narrow, double t) {
+        static const double rate[X3TILE_COUNT] = {0.6, 0.68, 0.84, 1.0};
+        const bool whole = red % 32 == 0, strided = q.sh * q.sw > 1;
+        return t * (rate[tile] * (whole ? 0.88 : 1.0) + (staged > 160000000 ? 0.2 : 0.0) +
+                    (narrow && q.G > 2 && red <= 16 && taps >= 25 ? strided ? 0.5 : 0.2 : 0.0) +
+                    (tile == X3TILE_48x128 && !whole && red > 80 && taps > 1 ? 0.45 : 0.0));
+    };
+    static const double rate_w[X3WTILE_COUNT] = {0.58, 0.68, 0.87};
+    const double terms_f = of_f +
+                           gemm(x.fwd_tile, x.Cgp, q.kh * q.kw, xb, true, tx_f) +
+                           (x.fwd_splits > 1 ? 3.5 * us + 0.06 * tx_f : 0.0) + 0.07e-12 * fpart;
+    const double terms_d = of_d +
+                           gemm(x.data_tile, x.Kgp, q.Th * q.Tw, db, false, tx_d) +
+                           (x.data_splits > 1 ? 3.5 * us + 0.12 * tx_d : 0.0) + 0.08e-12 * dpart;
+    const double terms_w = of_w + tx_w * (rate_w[x.wgt_tile] + (xb + db > 160000000 ? 0.2 : 0.0)) +
+                           0.055e-12 * wpart;
+    const bool f = terms_f < spare_f * float_f;
+    const bool d = terms_d < spare_d * float_d;
+    const bool w = terms_w < spare_w * float_w;
+    // the weight gradient of a call that also forms the data gradient shares
+    // its staged top gradient, on the float path its mask pass
+    const bool wj = terms_w - share < spare_j * (float_w - mask);
     x.fwd = can_f && (forced >= 0 ? (forced & 1) != 0 : f);
     x.data = can_d && (forced >= 0 ? (forced & 2) != 0 : d);
     x.wgt = can_w && (forced >= 0 ? (forced & 4) != 0 : w);
@@ -768,9 +818,8 @@ void plan_x3(ConvPlan* p, double est_f, double est_d, double est_w)
     // top of the mask pass that gradient needs (measured: conv1 at N = 256
     // 1336 us on the float path, 1401 with the data gradient alone on the
     // terms); a call for the data gradient alone follows the same rule, so
-    // that both forms of a backward pass give the same bits
-    x.data = x.data && (forced >= 0 || x.wgt_joint ||
-                        of_d + (q.relu ? bt * 2.7e-13 : 0) + 0.76 * tx_d < 0.8 * float_d);
+    // that its bits are those of a call for both
+    x.data = x.data && (forced >= 0 || x.wgt_joint || terms_d + mask < spare_m * float_d);
 
     if (x.fwd) {
         x.off_wp = align_up(xb, kWsAlign);

@@ -417,3 +417,37 @@ def test_workspace_preferred_holds_the_terms():
         if cc.conv_uses_terms(d, cc.PASS_BACKWARD):
             assert cc.conv_workspace_preferred(d, cc.PASS_BACKWARD) >= xb + db
     assert min(took) > 100, took
+
+
+# pass, N, C, H, W, K, k, stride, pad, group, relu; us on the float path and on
+# terms (both measured)
+SLOWER_ON_TERMS = [
+    (0, 494, 200, 37, 21, 28, 7, 2, 0, 4, True),     # 578, 919
+    (0, 91, 40, 68, 21, 184, 11, 2, 2, 8, True),     # 179, 299
+    (0, 7, 456, 109, 202, 4, 3, 1, 0, 2, False),     # 525, 734
+    (0, 16, 40, 67, 98, 32, 11, 2, 4, 8, True),      # 200, 260
+    (0, 68, 279, 34, 161, 2, 3, 1, 0, 1, True),      # 717, 929
+    (0, 3, 96, 83, 185, 48, 11, 1, 0, 16, True),     # 385, 477
+    (0, 39, 256, 24, 169, 585, 1, 1, 0, 1, True),    # 449, 531
+    (1, 18, 448, 123, 50, 256, 3, 1, 1, 16, False),  # 257, 305
+    (2, 6, 157, 11, 29, 240, 7, 1, 0, 1, False),     # 61, 73
+    (2, 2, 44, 4, 205, 316, 7, 1, 3, 1, False),      # 48, 56
+    (2, 83, 15, 65, 28, 266, 3, 1, 0, 1, False),     # 202, 226
+]
+FASTER_ON_TERMS = [
+    (0, 256, 96, 27, 27, 256, 5, 1, 2, 2, True),     # 879, 590
+    (1, 256, 96, 27, 27, 256, 5, 1, 2, 2, True),     # 959, 765
+    (2, 256, 96, 27, 27, 256, 5, 1, 2, 2, True),     # 975, 721
+    (0, 16, 256, 13, 13, 384, 3, 1, 1, 1, True),     # 68, 49
+    (1, 32, 384, 13, 13, 384, 3, 1, 1, 2, True),     # 114, 73
+    (2, 64, 384, 13, 13, 256, 3, 1, 1, 2, True),     # 125, 89
+    (1, 256, 20, 12, 12, 50, 5, 1, 0, 1, False),     # 88, 61
+]
+
+
+@pytest.mark.parametrize("case", SLOWER_ON_TERMS + FASTER_ON_TERMS)
+def test_terms_where_they_are_faster(case):
+    """The rule that picks the path, on layers of which both were timed."""
+    pas, N, C, H, W, K, k, s, p, g, relu = case
+    d = cc.conv_desc((N, C, H, W), (K, C // g, k, k), s, p, g, relu)
+    assert cc.conv_uses_terms(d, pas) == (case in FASTER_ON_TERMS)
