@@ -433,12 +433,14 @@ __device__ __forceinline__ float sum_parts(float t, int part, int col)
     }
 }
 
-// Parts for `count` outputs: eight where one thread per output would give
-// the device less than four waves a SIMD unit and each has eight terms or more
-// (one image through CaffeNet, MI355X, the five forward reduces: 39.9 us -> 23.8).
+// Parts for `count` outputs: eight where they are few and the splits many, one
+// thread an output otherwise.  us, one part / eight: 1024 outputs 3.8 / 2.6 with
+// 12 splits, 10.2 / 3.0 with 128; 32768 3.9 / 3.8, 9.9 / 3.6; 131072 4.4 / 3.9
+// with 32 splits, 3.9 / 4.2 with 16; 262144 3.9 / 7.0 with 16, 6.1 / 6.3 with 32
+// (one image through CaffeNet, the five forward reduces: 39.9 -> 23.8).
 static bool split_in_parts(int64_t count, int splits)
 {
-    return count <= 1024 * 256 && splits >= 8;
+    return (count <= 32 * 1024 && splits >= 12) || (count <= 128 * 1024 && splits >= 32);
 }
 
 // Split-K partials, then the bias and ReLU.

@@ -229,13 +229,23 @@ def test_split_k(case, splits, blocked, overrides):
 
 
 @pytest.mark.parametrize("case", SPLIT_CASES)
-@pytest.mark.parametrize("splits", [8, 11])
+@pytest.mark.parametrize("splits", [8, 11, 18, 33])
 def test_split_k_in_parts(case, splits, overrides):
-    """Eight splits and more: the reduces add them in eight parts, whole and
-    ragged."""
+    """Twelve splits and more (of as many stages): the reduces of these few
+    outputs add them in eight parts, whole and ragged."""
     overrides.setenv("CAFFE_CONV_FWD_SPLITS", str(splits))
     overrides.setenv("CAFFE_CONV_DGRAD_SPLITS", str(splits))
     run_case(*case, relu=True, bias=True)
+
+
+@pytest.mark.parametrize("C,K,splits", [(704, 128, 11), (768, 128, 12), (768, 129, 12),
+                                        (496, 512, 31), (512, 512, 32), (512, 513, 32)])
+def test_split_k_parts_edges(C, K, splits, overrides):
+    """Outputs (256 K) and splits at the edges of the rule that picks the
+    reduce: 2^15 with 11 and 12 splits, 2^17 with 31 and 32, and past them."""
+    overrides.setenv("CAFFE_CONV_X3", "0")
+    overrides.setenv("CAFFE_CONV_FWD_SPLITS", str(splits))
+    run_case(1, C, 16, 16, K, 1, 1, 1, 1, 0, 0, 1, relu=True, bias=True)
 
 
 @pytest.mark.parametrize("case", SPLIT_CASES)

@@ -214,9 +214,9 @@ def test_few_samples(N, rows, overrides):
 
 
 @pytest.mark.parametrize("case", [(3, 160, 70), (8, 16 * 33, 130), (2, 2048, 64)])
-@pytest.mark.parametrize("splits", [7, 8, 9, 33])
+@pytest.mark.parametrize("splits", [7, 8, 9, 11, 12, 13, 17, 33])
 def test_few_samples_gemm_splits(case, splits, overrides):
-    """The GEMM path on few samples, its partials added in one part (below 8
+    """The GEMM path on few samples, its partials added in one part (below 12
     splits) and in eight, ragged and whole."""
     overrides.setenv("CAFFE_FC_FEW", "0")
     overrides.setenv("CAFFE_FC_SPLITS_F", str(splits))
