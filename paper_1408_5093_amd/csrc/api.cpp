@@ -172,6 +172,15 @@ double plan_splits(int M, int ncol, int R, int tile, int cus, int forced, int* s
                             splits, sps, groups);
 }
 
+// The next split count with fewer stages a split than sp splits of n take, n
+// being ceil(n / sp) = per: the models below only grow between the two, so they
+// are tried at the first count of each (a reduction of 800 stages 56 times, not
+// 800: 2 of the 8 us of a small layer's plan).  past: no count has fewer.
+int64_t next_split(int64_t n, int64_t per, int64_t past)
+{
+    return per > 1 ? (n - 1) / (per - 1) + 1 : past;
+}
+
 // plan_splits for tiles of tm x tn whose workgroups take t_stage per stage,
 // nst stages in all; returns the modelled time of the plan.
 double plan_splits_tile(int M, int ncol, int64_t nst, int tm, int tn, double t_stage, int cus,
@@ -183,12 +192,13 @@ double plan_splits_tile(int M, int ncol, int64_t nst, int tm, int tn, double t_s
     const double t_byte = 1.0 / 4e12;  // partials at ~4 TB/s
     int64_t best = 1;
     double best_t = -1, t1 = 0;
-    for (int64_t sp = 1; sp <= nst; ++sp) {
+    for (int64_t sp = 1, per; sp <= nst; sp = next_split(nst, per, nst + 1)) {
+        per = (nst + sp - 1) / sp;
         const double part = sp > 1 ? 8.0 * sp * groups * M * ncol : 0.0;
         if (part / 2 > (double)kMaxTensorBytes)
             break;
         const int64_t load = (tiles * sp + cus - 1) / cus;  // workgroups per unit
-        const double t = (double)load * ((nst + sp - 1) / sp) * t_stage * (load == 1 ? 1.1 : 1.0) +
+        const double t = (double)load * per * t_stage * (load == 1 ? 1.1 : 1.0) +
                          part * t_byte;
         if (sp == 1)
             t1 = t;
@@ -552,9 +562,10 @@ int plan_bf16(ConvPlan* p)
         double best = 1e30;
         const int64_t lo = std::max<int64_t>(1, std::min(max_splits, target / tiles));
         const int64_t hi = std::max(lo, std::min(max_splits, 2 * splits));
-        for (int64_t sp = lo; sp <= hi; ++sp) {
+        const int64_t stages = (ncol + tk - 1) / tk;
+        for (int64_t sp = lo, nst; sp <= hi; sp = next_split(stages, nst, hi + 1)) {
             const int64_t rounds = (tiles * sp + cus - 1) / cus;
-            const int64_t nst = ((ncol + sp - 1) / sp + tk - 1) / tk;
+            nst = (stages + sp - 1) / sp;
             const double t = rounds * (nst + 5) * t_stage + 8.0 * sp * rw * q.K / 4e12;
             if (t < best) {
                 best = t;
@@ -767,9 +778,10 @@ void plan_x3(ConvPlan* p, double est_f, double est_d, double est_w)
         // kernel's length it is still the smaller one (measured against 64
         // bits: conv2's weight gradient 4.3e-7 against 5.1e-7)
         const int64_t lo = std::max<int64_t>(1, std::min<int64_t>(max_splits, (q.splits + 3) / 4));
-        for (int64_t sp = lo; sp <= std::max(lo, hi); ++sp) {
+        const int64_t stages = (ncol + kX3TK - 1) / kX3TK, last = std::max(lo, hi);
+        for (int64_t sp = lo, nst; sp <= last; sp = next_split(stages, nst, last + 1)) {
             const int64_t rounds = (tiles * sp + cus - 1) / cus;
-            const int64_t nst = ((ncol + sp - 1) / sp + kX3TK - 1) / kX3TK;
+            nst = (stages + sp - 1) / sp;
             const double t = rounds * (nst + 6) * t_stage(wtm, 256) + 8.0 * sp * rw * q.K / 4e12;
             if (t < best) {
                 best = t;
