@@ -139,8 +139,9 @@ size_t caffe_conv_workspace_bytes(const caffe_conv_desc* desc, int32_t pass);
  * 256 pixels, W and Wo, their staging's limit) run on the bf16 matrix
  * instructions, each float operand, subnormals included, staged in the
  * workspace as the exact sum of three bf16 terms; a product loses at most 2^-24
- * of itself, sums and results are float, and results that are infinite or NaN
- * are formed in float arithmetic.  With a workspace of at least
+ * of itself, sums and results are float.  Results that are infinite, NaN or past
+ * 2^96, or that an operand of 2^112 or more enters, are formed one by one in
+ * float arithmetic (many times slower: blobs that diverge).  With a workspace of at least
  * caffe_conv_workspace_size but less than this they run on the float
  * instructions, which stage nothing.  Where the float kernels' split partials
  * need as much as the staging, the two sizes are equal and the terms always
