@@ -141,11 +141,11 @@ size_t caffe_conv_workspace_bytes(const caffe_conv_desc* desc, int32_t pass);
  * workspace as the exact sum of three bf16 terms; a product loses at most 2^-24
  * of itself, sums and results are float.  Results that are infinite, NaN or past
  * 2^96, or that an operand of 2^112 or more enters, are formed one by one in
- * float arithmetic (many times slower: blobs that diverge).  With a workspace of at least
- * caffe_conv_workspace_size but less than this they run on the float
- * instructions, which stage nothing.  Where the float kernels' split partials
- * need as much as the staging, the two sizes are equal and the terms always
- * run, in caffe_conv_forward_noalloc too.  The two forms differ by rounding; so
+ * float arithmetic (many times slower: blobs that diverge).  With a workspace
+ * of at least caffe_conv_workspace_size but less than this they run on the
+ * float instructions, which stage nothing.  Where the float kernels' split
+ * partials need as much as the staging, the two sizes are equal and the terms
+ * always run, in caffe_conv_forward_noalloc too.  The two forms differ by rounding; so
  * may the weight gradient of a call for both gradients and of a call for the
  * weights alone, which decide for themselves.  Host-only. */
 int caffe_conv_workspace_preferred(const caffe_conv_desc* desc, int32_t pass, size_t* bytes);
